@@ -42,6 +42,15 @@ __device__ __forceinline__ cd cdiv(cd a, cd b)
     return mk((a.r * b.r + a.i * b.i) * inv, (a.i * b.r - a.r * b.i) * inv);
 }
 
+// the same with a cubic step, r (1 + e + e^2) for e = 1 - q r: one FMA more, and the
+// estimate's 2^-24 leaves 2^-72
+__device__ __forceinline__ double rcp64c(double q)
+{
+    const double r = __builtin_amdgcn_rcp(q);
+    const double e = fma(-q, r, 1.0);
+    return fma(fma(e, e, e), r, r);
+}
+
 // Plan tables and argument tables are read-only while a kernel runs.  Reading
 // them through the constant address space tells the compiler so: wave-uniform
 // reads then become scalar loads into SGPR operands even in the serving
@@ -64,6 +73,43 @@ __device__ cd csqrt_principal(double a, double b)
     }
     double t = sqrt(0.5 * (r - a));
     return mk(fabs(b) / (2.0 * t), copysign(t, b));
+}
+
+// sin and cos of an angle of at most a few turns, to about an ulp: the angle
+// less the nearest multiple of pi/2 (in two parts, exact in the first FMA), the
+// Taylor series to x^17 and x^18 (remainders below 1e-19 at pi/4).  The library's
+// sincos carries a reduction for arguments of any size, whose code a small
+// scan's waves, each at most a node or two long, would wait to fetch.
+__device__ __forceinline__ void sincos_turn(double a, double *sn, double *cs)
+{
+    constexpr double kHi = 1.57079632679489655800, kLo = 6.12323399573676603587e-17;  // pi/2
+    const double q = rint(a * 0.63661977236758134308);
+    double x = fma(-q, kHi, a);
+    x = fma(-q, kLo, x);
+    const double z = x * x;
+    double s = 1.0 / 355687428096000.0;                       // 1/17!
+    s = fma(s, -z, 1.0 / 1307674368000.0);                    // 1/15!
+    s = fma(s, -z, 1.0 / 6227020800.0);
+    s = fma(s, -z, 1.0 / 39916800.0);
+    s = fma(s, -z, 1.0 / 362880.0);
+    s = fma(s, -z, 1.0 / 5040.0);
+    s = fma(s, -z, 1.0 / 120.0);
+    s = fma(s, -z, 1.0 / 6.0);
+    s = fma(s * -z, x, x);
+    double c = 1.0 / 6402373705728000.0;                      // 1/18!
+    c = fma(c, -z, 1.0 / 20922789888000.0);                   // 1/16!
+    c = fma(c, -z, 1.0 / 87178291200.0);
+    c = fma(c, -z, 1.0 / 479001600.0);
+    c = fma(c, -z, 1.0 / 3628800.0);
+    c = fma(c, -z, 1.0 / 40320.0);
+    c = fma(c, -z, 1.0 / 720.0);
+    c = fma(c, -z, 1.0 / 24.0);
+    c = fma(c, -z, 0.5);
+    c = fma(c, -z, 1.0);
+    const int k = (int)q & 3;
+    const double u = k & 1 ? c : s, w = k & 1 ? s : c;
+    *sn = k & 2 ? -u : u;
+    *cs = (k + 1) & 2 ? -w : w;
 }
 
 __device__ __forceinline__ double angle_between(double a, double b)
@@ -99,12 +145,29 @@ constexpr int kInfoResLong = 8;    // bits 8-15: k-leg residues of the long rota
 constexpr int kInfoGrpLong = 16;   // bits 16-23: (p-k)-leg poles of the long rotation
 constexpr int kInfoRValid = 1 << 24;
 
-template <bool POLES = false, class Args>
-__device__ int classify(const Args &a, double xr, double xi, int *res_sign, int *info = nullptr)
+// |x|, |Im sqrt x| and arg x, taken once per point; e^{i arg x} is x / |x|.  A
+// point's set-up is what bounds a small scan, whose every lane repeats it
+// (about 1,090 VALU instructions a wave when the class rule, its mirror test
+// and the ray each took atan2, hypot and sincos anew): one 64^2 scan at 64 x 32
+// + 16 nodes, 64 lanes per point, 13.1 -> 10.8 us; 128^2 at 64 x 49 tanh-sinh
+// nodes 26.2 -> 24.0 us.
+struct PointArg {
+    double r, v, phi;
+};
+
+__device__ __forceinline__ PointArg point_arg(double xr, double xi)
 {
-    cd sx = csqrt_principal(xr, xi);
-    double v = fabs(sx.i);
-    double phi = atan2(xi, xr);
+    PointArg p;
+    p.r = hypot(xr, xi);
+    const double t = sqrt(0.5 * (p.r + fabs(xr)));  // the larger component of sqrt x
+    p.v = xr < 0.0 ? t : (p.r > 0.0 ? fabs(xi) / (2.0 * t) : 0.0);
+    p.phi = atan2(xi, xr);
+    return p;
+}
+
+template <bool POLES = false, class Args>
+__device__ int classify(const Args &a, double v, double phi, int *res_sign, int *info = nullptr)
+{
     int rot;
     int mask = 0, lng = 0;  // residues of the short rotation; the kLong sets
     *res_sign = 0;
@@ -256,8 +319,8 @@ __device__ void split_boundaries(const Args &a, double xr, double xi, double *b)
 }
 
 template <bool SPLIT = false, bool POLES = false, class Args>
-__device__ PointCtx point_setup(const Args &a, double xr, double xi, int cls, int res_sign,
-                                int info = 0)
+__device__ PointCtx point_setup(const Args &a, double xr, double xi, double r, double phi, int cls,
+                                int res_sign, int info = 0)
 {
     PointCtx P;
     P.x1 = mk(xr + a.m1_re, xi + a.m1_im);
@@ -270,14 +333,13 @@ __device__ PointCtx point_setup(const Args &a, double xr, double xi, int cls, in
         for (int i = 0; i < 5; ++i) P.tb[i] = b[i];
     }
     if (cls == kY || cls == kYRes || cls == kLong) {
-        double phi = atan2(xi, xr);
-        double s, c;
-        sincos(phi, &s, &c);
-        P.dir = mk(c, s);
+        const double ir = rcp64c(r);
+        P.dir = mk(xr * ir, xi * ir);
         if (a.dim == 4) {
             P.dirD = cmul(P.dir, P.dir);
         } else if (a.dim == 3) {
-            sincos(0.5 * phi, &s, &c);
+            double s, c;
+            sincos_turn(0.5 * phi, &s, &c);
             P.dirD = cmul(P.dir, mk(c, s));
         } else {
             P.dirD = P.dir;
@@ -400,7 +462,7 @@ __device__ __forceinline__ bool outer_coeffs(const Args &a, const PointCtx &P, i
             h = 0.5 * L * wa;
         }
         double s, c;
-        sincos(psi, &s, &c);
+        sincos_turn(psi, &s, &c);
         const cd y = mk(a.lam2 * c, a.lam2 * s);
         U = cadd(P.x1, y);
         V2 = cmul(x4, y);
@@ -409,7 +471,7 @@ __device__ __forceinline__ bool outer_coeffs(const Args &a, const PointCtx &P, i
         if (a.dim == 3) {
             // the long arc's angle runs from phi -+ 2 pi back to 0 along the
             // contour: sqrt(y) = e^{i (psi -+ 2 pi)/2} Lambda = -e^{i psi/2} Lambda
-            sincos(0.5 * psi, &s, &c);
+            sincos_turn(0.5 * psi, &s, &c);
             const double lam = lng ? -a.lam : a.lam;
             f = mk(lam * c, lam * s);
         } else if (a.dim == 2) {
@@ -446,7 +508,7 @@ __device__ __forceinline__ bool outer_coeffs(const Args &a, const PointCtx &P, i
         else if (P.phi > 0.0 && t > P.phi) t -= 2.0 * M_PI;
         else if (P.phi < 0.0 && t < P.phi) t += 2.0 * M_PI;
         double s, c;
-        sincos(0.5 * t, &s, &c);
+        sincos_turn(0.5 * t, &s, &c);
         const double m = sqrt(hypot(y0.r, y0.i));
         return mk(m * c, m * s);
     };

@@ -272,11 +272,12 @@ __global__ void __launch_bounds__(64) obstruction_kernel(ScanArgs a, int n, doub
     const double xi = fma((double)ib + 0.5, a.d_im, a.im_lo);
     const bool real_hit = cut_hits_real_axis(a, xr, xi, n, T);
     int sign = 0, info = 0;
-    int cls = classify(a, xr, xi, &sign, &info);
+    const PointArg pa = point_arg(xr, xi);
+    int cls = classify(a, pa.v, pa.phi, &sign, &info);
     double ei = xi;
     int ecls = cls;
     if (cls == kMirror) {  // the scan evaluates the conjugate point, if it has a contour
-        ecls = classify(a, xr, -xi, &sign);
+        ecls = classify(a, pa.v, -pa.phi, &sign);
         if (ecls == kMirror || ecls == kSingular || ecls == kLong)
             cls = ecls = (info & kInfoRValid) ? kR : kLong;
         else

@@ -44,24 +44,27 @@ __device__ __forceinline__ void process_tile(const Args &a, int tile, int lane, 
     double xr = fma((double)ia + 0.5, a.d_re, a.re_lo);
     double xi = fma((double)ib + 0.5, a.d_im, a.im_lo);
     int sign = 0, info = 0;
-    int cls = valid ? classify<POLES>(a, xr, xi, &sign, &info) : kSingular;
+    const PointArg pa = point_arg(xr, xi);
+    double phi = pa.phi;
+    int cls = valid ? classify<POLES>(a, pa.v, phi, &sign, &info) : kSingular;
     int ecls = cls;
     if (cls == kMirror) {
         // evaluate at conj x and conjugate the result; if conj x has no
         // contour of its own, the real axis where it is valid at x, else the
         // long way round at x (info holds its sets)
         int sign_b = 0, info_b = 0;
-        ecls = classify<POLES>(a, xr, -xi, &sign_b, &info_b);
+        ecls = classify<POLES>(a, pa.v, -phi, &sign_b, &info_b);
         if (ecls == kMirror || ecls == kSingular || ecls == kLong) {
             cls = ecls = (info & kInfoRValid) ? kR : kLong;
             if (cls == kR) sign = info = 0;
         } else {
             xi = -xi;
+            phi = -phi;
             sign = sign_b;
             info = info_b;
         }
     }
-    const PointCtx pc = point_setup<SPLIT, POLES>(a, xr, xi, ecls, sign, info);
+    const PointCtx pc = point_setup<SPLIT, POLES>(a, xr, xi, pa.r, phi, ecls, sign, info);
 
     // The straight part's nodes, then the arc and residue nodes, in one
     // sequence k = s, s + L, ... per lane: two loops so that the arc's sine
@@ -314,7 +317,7 @@ __device__ void taylor_node(const Args &a, cd U0, double y, cd omega, int n, cd 
 template <bool SPLIT, bool POLES, class Args>
 __device__ __forceinline__ void jmu_wave_impl(const Args &a, double mu2, double *dst, int lane)
 {
-    const PointCtx pc = point_setup<SPLIT, POLES>(a, mu2, 0.0, kR, 0, 0);
+    const PointCtx pc = point_setup<SPLIT, POLES>(a, mu2, 0.0, mu2, 0.0, kR, 0, 0);
     double sr = 0.0, si = 0.0;
     cd acc[GF_MAX_TAYLOR + 1];
     for (int i = 0; i <= GF_MAX_TAYLOR; ++i) acc[i] = mk(0.0, 0.0);
