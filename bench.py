@@ -49,7 +49,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "scan_kernel_fp64_bench_workload_t
 FLOPS_FILE = os.path.join(ROOT, "profiles", "scan_kernel_fp64_bench_workload_flops.json")
 # the sources that define the scan kernels' machine code
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1205_0752_amd", "csrc", name)
-                  for name in ("gf_internal.h", "gf_device.h", "gf_kernels.hip")]
+                  for name in ("gf_internal.h", "gf_device.h", "gf_scan.h", "gf_scan_groups.hip",
+                               "gf_scan_pairs.hip", "gf_scan_fp32c.hip", "gf_kernels.hip")]
 
 
 def kernel_source_sha256() -> str:

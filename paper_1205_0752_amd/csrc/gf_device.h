@@ -42,13 +42,19 @@ __device__ __forceinline__ cd cdiv(cd a, cd b)
     return mk((a.r * b.r + a.i * b.i) * inv, (a.i * b.r - a.r * b.i) * inv);
 }
 
-// the same with a cubic step, r (1 + e + e^2) for e = 1 - q r: one FMA more, and the
-// estimate's 2^-24 leaves 2^-72
+// The same with a cubic step, r (1 + e + e^2) for e = 1 - q r: one FMA more, and the
+// estimate's 2^-24 leaves 2^-72 where Newton's e^2, always below the true value
+// and up to 2e-15, biases a sum of such terms.
 __device__ __forceinline__ double rcp64c(double q)
 {
     const double r = __builtin_amdgcn_rcp(q);
     const double e = fma(-q, r, 1.0);
     return fma(fma(e, e, e), r, r);
+}
+__device__ __forceinline__ cd cinv(cd b)
+{
+    const double inv = rcp64c(fma(b.r, b.r, b.i * b.i));
+    return mk(b.r * inv, -(b.i * inv));
 }
 
 // Plan tables and argument tables are read-only while a kernel runs.  Reading
@@ -371,17 +377,19 @@ __device__ PointCtx point_setup(const Args &a, double xr, double xi, double r, d
 // y for D = 4), or +-2 pi i y0^{(D-2)/2} at the residue.  Along the ray
 // y = e^{i phi} r, dy y^{(D-2)/2} = e^{i phi D/2} dr r^{(D-2)/2}; the table holds
 // the real weight dr r^{(D-2)/2}.
-// Radial node k of the straight part: r and the real weight dr r^{(D-2)/2}.
+// Radial node k of the straight part: r, the real weight dr r^{(D-2)/2} and,
+// where the caller takes it, 1/r.
 // Unsplit, from the plan's table; split, from the base GL rule of order n_r/4
 // (table: xi[m], w[m]) mapped onto piece k / m of the point's boundaries.
 template <bool SPLIT, class Args>
 __device__ __forceinline__ void radial_node(const Args &a, const PointCtx &P, int k, double &r,
-                                            double &g)
+                                            double &g, double *rinv = nullptr)
 {
     const auto *rad = ro(a.rad);
     if (!SPLIT) {
         r = rad[k];
         g = rad[2 * a.n_r + k];
+        if (rinv) *rinv = rad[a.n_r + k];
         return;
     }
     const int m = a.n_r >> 2;
@@ -396,6 +404,38 @@ __device__ __forceinline__ void radial_node(const Args &a, const PointCtx &P, in
     r = expm1(fma(h, rad[i] + 1.0, lo));
     const double dr = h * rad[m + i] * (1.0 + r);
     g = a.dim == 4 ? dr * r : (a.dim == 3 ? dr * sqrt(r) : dr);
+    if (rinv) *rinv = rcp64c(r);
+}
+
+// The straight part for the grouped sums: y = dir r, V^2 = 4 x dir r, and
+//   1 / V^2           = kappa / r,              kappa = 1 / (4 x dir),
+//   (x - y)^2 / V^2   = k2 (r - a)^2 / r + c0 + b0 / r.
+// On a ray x = |x| dir, so with a = |x| the square is exact as it stands and k2 =
+// kappa dir^2 = 1 / (4 |x|) (c0 = b0 = 0); on the real axis (dir = 1) with a = Re x,
+// (x - r)^2 = (r - a)^2 - 2i Im x (r - a) - Im x^2.
+struct StraightCtx {
+    cd kappa, k2, c0, b0;
+    double a;
+};
+
+template <class Args>
+__device__ __forceinline__ StraightCtx straight_ctx(const Args &a, const PointCtx &P, double absx,
+                                                    bool real_axis)
+{
+    StraightCtx s;
+    const cd x = mk(P.x1.r - a.m1_re, P.x1.i - a.m1_im);
+    s.kappa = cinv(cmul(mk(4.0 * x.r, 4.0 * x.i), P.dir));
+    if (real_axis) {
+        s.a = x.r;
+        s.k2 = s.kappa;
+        s.c0 = cmul(s.kappa, mk(0.0, -2.0 * x.i));
+        s.b0 = cmul(s.kappa, mk(-(x.i * x.i), 2.0 * x.i * x.r));
+    } else {
+        s.a = absx;
+        s.k2 = mk(0.25 * rcp64c(absx), 0.0);
+        s.c0 = s.b0 = mk(0.0, 0.0);
+    }
+    return s;
 }
 
 // The k-leg pole sum P2(y) = sum_b c2_b / (y + m2_b^2).
@@ -699,11 +739,12 @@ __device__ __forceinline__ void pair_sums64(const double *table, int npair, doub
     if (NUM) *T2 = y0 + y1;
 }
 
-template <int SCALE = 1>
+template <int SCALE = 1, bool DIRECT = false>
 __device__ __forceinline__ cd angular_sum64(const double *table, int npair, double wmid, cd U,
                                             cd V2in, bool scale_rt = true)
 {
     // SCALE 1: always rescale; 0: never; -1: as scale_rt says
+    // DIRECT: always the direct denominators
     const bool scale = SCALE == 1 || (SCALE == -1 && scale_rt);
     // sum_j 2w_j / D_j = sum_j 2w_j conj(D_j) / |D_j|^2 with D_j = U^2 - V^2 z_j^2,
     // and conj(D_j) = conj(U^2) - conj(V^2) z_j^2, so the pair sum is
@@ -722,7 +763,7 @@ __device__ __forceinline__ cd angular_sum64(const double *table, int npair, doub
         v2i = ldexp(v2i, -e);
     }
     double T0, T1;
-    if (near_cut_sq(u2r, u2i, v2r, v2i))
+    if (DIRECT || near_cut_sq(u2r, u2i, v2r, v2i))
         pair_sums64<false>(table, npair, u2r, u2i, v2r, v2i, T0, T1);
     else
         pair_sums64<true>(table, npair, u2r, u2i, v2r, v2i, T0, T1);
@@ -735,6 +776,154 @@ __device__ __forceinline__ cd angular_sum64(const double *table, int npair, doub
     cd A = cmul(U, mk(sr, -si));
     if (wmid != 0.0) A = cadd(A, cdiv(mk(wmid, 0.0), U));
     return A;
+}
+
+// The grouped angular sum.  With sigma = U^2 / V^2 = 1 + e and h = U / V^2,
+//   A = sum_j 2w_j U / (U^2 - V^2 s_j) = h sum_j 2w_j / (sigma - s_j),
+// and the folded nodes, spread over a.n_grp groups of eight, enter as one
+// rational function W N(v) / P(v) per group, N and P monic with real coefficients
+// from the plan's tables (group_table), so that each is one FMA per
+// coefficient and component on the powers v^2 .. v^8, which a node forms once
+// for all groups.  Two groups share one reciprocal.
+//
+// What bounds it: FP64 VALU issue (98 % of the launch's cycles), as everywhere
+// in the scan.  A group takes 42 issue slots (28 for P and N, 6 for |P|^2 and N
+// conj P, 5 for its share of the reciprocal, 3 to scale and add) where the pair
+// sums take 59 for the same eight pairs; a node adds 28 for the powers.
+// Measured, pairs to groups: 1024^2 at 256 x 128 + 16 nodes 4.19 -> 3.43 ms (2.31e9
+// -> 1.89e9 wave VALU instructions), 2048^2 at 512 x 256 59.9 -> 46.4 ms, pole sums
+// (two poles a leg) on 512^2 at 256 x 128 2.43 -> 1.90 ms, 128^2 at 256 x 128 (16
+// lanes) 91 -> 75 us.  Sixteen nodes a group would take 38 slots per eight but twice
+// the powers and lose the square of the accuracy.  The matrix cores are no
+// help: v_mfma_f64_16x16x4 takes 107 cycles for what 16 FMAs do in 73, and the two
+// do not overlap.
+//
+// Accuracy: an expansion about one centre loses sum |coefficient| |v|^k / |P|.
+// There are two tables.  v = e, about the cut's end s = 1: P = prod (e + 1 - s_j) has
+// only positive coefficients, so nothing is lost for Re e >= 0 however close to
+// the end, and little where |Im e| >= min(2, 4.5 |e|) |Re e| or |e| >= 3 (at most 45
+// eps of the sum, 3 in the median).  That covers nearly all nodes of a ray, where
+// e = (|x| - r)^2 / (4 |x| r) plus a term of order m1^2 / |x|.  v = e + 1/2, about
+// the middle, for the rest: a group's nodes being spread over (0, 1), the loss
+// stays below about 10 where |sigma|^2 + |e|^2 <= 6 |sigma| |e|, down to the ratio
+// kCutSensitivity from the cut (at most 46 eps, 1.7 in the median).  The pair
+// sums' quadratic loses up to 45 to 90 eps at its limit, 4 in the median
+// there.  Nodes that neither takes (0.5 to 3 % of a scan, 6 % of one along the
+// cut) and |e| >= 2^30 (two groups' |P|^2 multiply up to |v|^32) or V^2 = 0 run
+// over the pairs.
+__device__ __forceinline__ bool group_end(cd e)
+{
+    const double im2 = e.i * e.i, mag = fma(e.r, e.r, im2);
+    const double neg = fmin(e.r, 0.0);
+    // false for NaN and infinities
+    return (im2 >= fmin(4.0, 20.0 * mag) * (neg * neg) || mag >= 9.0) && mag < 0x1p60;
+}
+
+__device__ __forceinline__ bool group_middle(cd e)
+{
+    const double im2 = e.i * e.i, sr = e.r + 1.0;
+    const double me = fma(e.r, e.r, im2), ms = fma(sr, sr, im2);
+    const double d = sr - fmin(fmax(sr, 0.0), 1.0), d2 = fma(d, d, im2);
+    const double t = ms + me;
+    return t * t <= 36.0 * (ms * me) && me < 0x1p60 &&
+           fma(2.0, ms, 2.0) <= kCutSensitivity * kCutSensitivity * d2;
+}
+
+// S = sum_j 2w_j / (sigma - s_j) over n_grp groups, from a table about v's centre.
+__device__ __forceinline__ cd group_sums(const double *table, int n_grp, cd v)
+{
+    static_assert(kGroupNodes == 8, "the powers and coefficients below are written for eight");
+    const auto *t = ro(table);
+    double c[9], d[9];  // v^k = c[k] + i d[k]
+    c[1] = v.r;
+    d[1] = v.i;
+    auto square = [&](int k) {
+        c[2 * k] = fma(c[k], c[k], -(d[k] * d[k]));
+        d[2 * k] = (c[k] + c[k]) * d[k];
+    };
+    auto times = [&](int k, int m) {
+        c[k + m] = fma(c[k], c[m], -(d[k] * d[m]));
+        d[k + m] = fma(c[k], d[m], d[k] * c[m]);
+    };
+    square(1);
+    times(1, 2);
+    square(2);
+    times(2, 3);
+    square(3);
+    times(3, 4);
+    square(4);
+    // Coefficients of one group in scalar registers.  A group's load is issued
+    // once the one before it has arrived and is waited for after that group's
+    // sums, so that a wave alone on its SIMD does not wait the whole of it.
+    auto load = [](const auto *p, double (&q)[kGroupDoubles]) {
+#pragma unroll
+        for (int k = 0; k < kGroupDoubles; ++k) q[k] = p[k];
+    };
+    auto poly = [&](const double (&a)[kGroupDoubles], double &pr, double &pi, double &nr, double &ni,
+                    auto next) {
+        pr = fma(a[7], c[7], c[8]);
+        __builtin_amdgcn_sched_barrier(0);
+        next();
+        __builtin_amdgcn_sched_barrier(0);
+        pi = fma(a[7], d[7], d[8]);
+        nr = fma(a[14], c[6], c[7]);
+        ni = fma(a[14], d[6], d[7]);
+#pragma unroll
+        for (int k = 6; k > 0; --k) {
+            pr = fma(a[k], c[k], pr);
+            pi = fma(a[k], d[k], pi);
+            if (k < 6) {
+                nr = fma(a[8 + k], c[k], nr);
+                ni = fma(a[8 + k], d[k], ni);
+            }
+        }
+        pr += a[0];
+        nr += a[8];
+    };
+    double sr = 0.0, si = 0.0;
+    double ca[kGroupDoubles], cb[kGroupDoubles];
+    load(t, ca);
+    int g = 0;
+    for (; g + 2 <= n_grp; g += 2, t += 2 * kGroupDoubles) {
+        double pr, pi, nr, ni, qr, qi, mr, mi;
+        poly(ca, pr, pi, nr, ni, [&] { load(t + kGroupDoubles, cb); });
+        const double wp = ca[15];
+        poly(cb, qr, qi, mr, mi, [&] { load(t + 2 * kGroupDoubles, ca); });
+        const double p2 = fma(pr, pr, pi * pi), q2 = fma(qr, qr, qi * qi);
+        const double inv = rcp64c(p2 * q2);
+        const double rp = wp * (q2 * inv), rq = cb[15] * (p2 * inv);
+        sr = fma(rp, fma(nr, pr, ni * pi), sr);
+        si = fma(rp, fma(ni, pr, -(nr * pi)), si);
+        sr = fma(rq, fma(mr, qr, mi * qi), sr);
+        si = fma(rq, fma(mi, qr, -(mr * qi)), si);
+    }
+    if (g < n_grp) {
+        double pr, pi, nr, ni;
+        poly(ca, pr, pi, nr, ni, [] {});
+        const double rp = ca[15] * rcp64c(fma(pr, pr, pi * pi));
+        sr = fma(rp, fma(nr, pr, ni * pi), sr);
+        si = fma(rp, fma(ni, pr, -(nr * pi)), si);
+    }
+    return mk(sr, si);
+}
+
+// <1/(U - V z)> by the groups, given e = U^2 / V^2 - 1 and h = U / V^2; pairs()
+// gives it where no table applies.  Both run one after the other in a wave
+// whose lanes differ.  MIDDLE: with the second table, worth its code where
+// the lanes of a wave are points of one tile at neighbouring nodes; with many
+// lanes per point a wave spans a whole contour, and its few nodes near the cut
+// would bring the third sum into every wave.
+template <bool MIDDLE, class Args, class PairsFn>
+__device__ __forceinline__ cd angular_sum_grouped(const Args &a, cd e, cd h, PairsFn pairs)
+{
+    cd S;
+    if (group_end(e))
+        S = group_sums(a.grp, a.n_grp, e);
+    else if (MIDDLE && a.grp_mid && group_middle(e))
+        S = group_sums(a.grp + kGroupDoubles * a.n_grp, a.n_grp, mk(e.r + 0.5, e.i));
+    else
+        return pairs();
+    return cmul(h, S);
 }
 
 // Numerators in p.k: with p.k = (V/2) z, each folded pair gives
@@ -944,6 +1133,34 @@ __device__ __forceinline__ cd angular_sum_p(const Args &a, cd U, cd V2, int set 
         const cd Ua = mk(U.r + (q[0] - a.m1_re), U.i + (q[1] - a.m1_im));
         const double sg = neg >> p & 1 ? -1.0 : 1.0;
         A = cadd(A, cmul(mk(sg * q[2], sg * q[3]), angular_sum<PREC>(a, Ua, V2)));
+    }
+    return A;
+}
+
+// The same over the rule's groups (FP64, a.n_grp > 0, no numerator), given x + y,
+// iv = 1 / V^2 and a function for e0 = (x - y)^2 / V^2: with U = x + y + m^2,
+//   e = U^2 / V^2 - 1 = e0 + m^2 (2 (x + y) + m^2) iv.
+// The first form loses about 3 eps (1 + 1/|e|) of e, so the second (eps (1 +
+// |e|^-1/2) from the rounding of x - y) is taken for |e| < 1/2.  pairs(U) gives
+// the sum where no table applies.
+template <bool POLES, bool MIDDLE, class Args, class E0Fn, class PairsFn>
+__device__ __forceinline__ cd angular_sum_grouped_p(const Args &a, cd xy, cd iv, E0Fn e0,
+                                                    PairsFn pairs, int set = ~0, int neg = 0)
+{
+    auto one = [&](cd m) {
+        const cd U = cadd(xy, m), h = cmul(U, iv);
+        cd e = cmul(U, h);
+        e.r -= 1.0;
+        if (fma(e.r, e.r, e.i * e.i) < 0.25) e = cadd(e0(), cmul(iv, cmul(m, cadd(xy, U))));
+        return angular_sum_grouped<MIDDLE>(a, e, h, [&] { return pairs(U); });
+    };
+    if (!POLES) return one(mk(a.m1_re, a.m1_im));
+    cd A = mk(0.0, 0.0);
+    for (int p = 0; p < a.n1; ++p) {
+        if (!(set >> p & 1)) continue;
+        const auto *q = &a.p1[4 * p];
+        const double sg = neg >> p & 1 ? -1.0 : 1.0;
+        A = cadd(A, cmul(mk(sg * q[2], sg * q[3]), one(mk(q[0], q[1]))));
     }
     return A;
 }

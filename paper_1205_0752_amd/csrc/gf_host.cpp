@@ -144,7 +144,7 @@ void radial_table(int nr, double lambda2, int dim, int split, std::vector<double
         double y = std::expm1(t);
         double dy = 0.5 * T * gw[i] * (1.0 + y);
         rad[i] = y;
-        rad[nr + i] = std::sqrt(y);
+        rad[nr + i] = 1.0 / y;
         rad[2 * nr + i] = dim == 4 ? dy * y : (dim == 3 ? dy * std::sqrt(y) : dy);
     }
 }
@@ -217,6 +217,66 @@ void angular_tables(int na, int rule, int dim, std::vector<double> &ang,
     }
 }
 
+// The grouped form of the angular sum (angular_sum_grouped in gf_device.h) costs
+// about 42 issue slots per group of eight folded nodes (four more for an odd
+// last group) and 28 per contour node for the powers; pair by pair it is 59
+// slots per eight pairs, 31 per four, 11 per single pair and 12 for a middle
+// node.  The groups are taken where they save a tenth, which pays for their
+// larger code: from 34 pairs on always (16 pairs, 64^2 points at 64 lanes each:
+// 11.9 us in groups, 11.0 by pairs; 64 pairs: 19.2 and 20.6).
+int group_count(int na, int rule)
+{
+    (void)rule;
+    const int np = na / 2, nodes = np + na % 2;
+    const int groups = (nodes + kGroupNodes - 1) / kGroupNodes;
+    const int grouped = 42 * groups + 4 * (groups % 2) + 28;
+    const int single = 59 * (np / 8) + 31 * (np % 8 / 4) + 11 * (np % 4) + 12 * (na % 2);
+    return 10 * grouped < 9 * single ? groups : 0;
+}
+
+size_t group_doubles(int na, int rule)
+{
+    // one group more than the tables hold: the sums load a group ahead
+    const size_t n = group_count(na, rule);
+    return n ? kGroupDoubles * (n * (group_has_middle(rule) ? 2 : 1) + 1) : 0;
+}
+
+// Group g takes every n_grp-th folded node (s, 2w), an odd rule's middle node
+// being (0, w_mid), so that each spreads over (0, 1):
+//   sum_j 2w_j / (sigma - s_j) = W N(v) / P(v),   v = sigma - centre,
+// P(v) = prod (v - t_j), t_j = s_j - centre, N the matching monic numerator and W
+// the sum of the weights.  Missing nodes are filled up with s = centre, weight
+// 0.  The first table's centre is s = 1, the second's 1/2.  Tanh-sinh has no
+// second one: half of its nodes lie within 1e-2 of s = 1, where an expansion
+// about the middle would cancel (up to 1e5 eps next to that end; about s = 1 at
+// most 16).  The products run in long double, so the coefficients are rounded
+// once.
+void group_table(int na, int rule, const std::vector<double> &ang, double wmid,
+                 std::vector<double> &grp)
+{
+    const int n_grp = group_count(na, rule), np = na / 2, nodes = np + na % 2;
+    grp.assign(group_doubles(na, rule), 0.0);
+    const int tables = group_has_middle(rule) ? 2 : 1;
+    for (int b = 0; b < tables * n_grp; ++b) {
+        const int g = b % n_grp;
+        const long double centre = b < n_grp ? 1.0L : 0.5L;
+        long double P[kGroupNodes + 1] = {1.0L}, N[kGroupNodes + 1] = {};
+        for (int k = 0; k < kGroupNodes; ++k) {
+            const int j = g + k * n_grp;
+            const long double s = j < np ? (long double)ang[3 * j] : (j < nodes ? 0.0L : centre);
+            const long double t = s - centre, w = j < np ? ang[3 * j + 1] : (j < nodes ? wmid : 0.0);
+            // N <- N (v - t) + w P, then P <- P (v - t)
+            for (int i = k + 1; i >= 0; --i) N[i] = (i > 0 ? N[i - 1] : 0.0L) - t * N[i] + w * P[i];
+            for (int i = k + 1; i >= 0; --i) P[i] = (i > 0 ? P[i - 1] : 0.0L) - t * P[i];
+        }
+        double *o = grp.data() + (size_t)kGroupDoubles * b;
+        const long double W = N[kGroupNodes - 1];
+        for (int i = 0; i < kGroupNodes; ++i) o[i] = (double)P[i];
+        for (int i = 0; i < kGroupNodes - 1; ++i) o[kGroupNodes + i] = (double)(N[i] / W);
+        o[kGroupDoubles - 1] = (double)W;
+    }
+}
+
 void arc_table(int nc, std::vector<double> &arc)
 {
     std::vector<double> ax, aw;
@@ -263,6 +323,8 @@ void fill_constants(ScanArgs &a, const gf_params &p, const gf_propagators *props
     a.n_r = q.n_radial;
     a.n_a = q.n_angular;
     a.n_arc = q.n_arc;
+    a.grp = nullptr;  // set with the tables where the sums run in groups
+    a.n_grp = a.grp_mid = 0;
     // poles: from props, or one pole per leg at the masses of p with residue 1
     a.poles = props ? 1 : 0;
     a.n1 = props ? props->n1 : 1;
@@ -465,6 +527,7 @@ constexpr long long kMinLanePairs[2] = {2048, 4096};  // FP64, FP32C
 int auto_lanes(const ScanArgs &base, int precision, const gf_grid &g)
 {
     const bool taylor = base.n_taylor > 0, split = base.split != 0, poles = base.poles != 0;
+    const int form = scan_form(base, precision);
     const long long rounds = kRounds;
     const long long pairs = (long long)((base.n_a + 1) / 2) * (poles ? base.n1 : 1);
     const long long nodes = (long long)base.n_r + base.n_arc + (poles ? base.n2 : 1);
@@ -473,7 +536,7 @@ int auto_lanes(const ScanArgs &base, int precision, const gf_grid &g)
         int ta;
         long long nt;
         tiles_for(g, l, &ta, &nt);
-        const long long slots = scan_resident_waves(precision, l, taylor, split, poles);
+        const long long slots = scan_resident_waves(form, l, taylor, split, poles);
         if (!fill && nt >= slots) fill = l;
         if (!want && nt >= rounds * slots) want = l;
         if (l > 1 && (nodes + l - 1) / l * pairs >= kMinLanePairs[precision == 1]) work = l;
@@ -542,7 +605,8 @@ void set_tail(ScanArgs &a, const gf_grid &g, int precision, int lanes)
     a.tail_tiles = a.tail_row0 = a.tail_tiles_a = 0;
     if (!(lanes == 1 || (precision == 1 && lanes == 2))) return;
     const long long slots =
-        scan_resident_waves(precision, lanes, a.n_taylor > 0, a.split != 0, a.poles != 0);
+        scan_resident_waves(scan_form(a, precision), lanes, a.n_taylor > 0, a.split != 0,
+                            a.poles != 0);
     if (a.n_tiles < kTailMinRounds * slots || g.n_re <= 0) return;
     int twb, thb, twt, tht;
     tile_shape(lanes, &twb, &thb);
@@ -612,12 +676,15 @@ int gf_plan_ex(const gf_params *params, const gf_propagators *props, const gf_qu
     int dev;
     if ((rc = gf::current_device(&dev)) != GF_OK) return rc;
 
-    std::vector<double> rad, ang, arc;
+    std::vector<double> rad, ang, arc, grp;
     std::vector<float> ang32;
     double wmid = 0.0;
     const int dim = params->dimension == 0 ? 4 : params->dimension;
     gf::radial_table(quad->n_radial, params->lambda2, dim, quad->radial_split, rad);
     gf::angular_tables(quad->n_angular, quad->angular_rule, dim, ang, ang32, &wmid);
+    // FP32C sums run pair by pair
+    const bool grouped = quad->precision == GF_PREC_FP64;
+    if (grouped) gf::group_table(quad->n_angular, quad->angular_rule, ang, wmid, grp);
     gf::arc_table(quad->n_arc, arc);
 
     const size_t off_rad = 0;
@@ -625,7 +692,8 @@ int gf_plan_ex(const gf_params *params, const gf_propagators *props, const gf_qu
     const size_t off_arc = off_ang + gf::align256(ang.size() * sizeof(double));
     const size_t off_jmu = off_arc + gf::align256(arc.size() * sizeof(double));
     const size_t off_a32 = off_jmu + 256;
-    const size_t total = off_a32 + gf::align256(ang32.size() * sizeof(float));
+    const size_t off_grp = off_a32 + gf::align256(ang32.size() * sizeof(float));
+    const size_t total = off_grp + gf::align256(grp.size() * sizeof(double));
 
     gf_plan_t *plan = new (std::nothrow) gf_plan_t();
     if (!plan) return fail(GF_ENOMEM, "host allocation failed");
@@ -645,8 +713,10 @@ int gf_plan_ex(const gf_params *params, const gf_propagators *props, const gf_qu
     } ups[] = {{off_rad, rad.data(), rad.size() * sizeof(double)},
                {off_ang, ang.data(), ang.size() * sizeof(double)},
                {off_arc, arc.data(), arc.size() * sizeof(double)},
-               {off_a32, ang32.data(), ang32.size() * sizeof(float)}};
+               {off_a32, ang32.data(), ang32.size() * sizeof(float)},
+               {off_grp, grp.data(), grp.size() * sizeof(double)}};
     for (const Up &u : ups) {
+        if (u.bytes == 0) continue;
         e = hipMemcpy(base + u.off, u.src, u.bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             gf_free(plan);
@@ -664,6 +734,9 @@ int gf_plan_ex(const gf_params *params, const gf_propagators *props, const gf_qu
     a.ang = reinterpret_cast<const double *>(base + off_ang);
     a.arc = reinterpret_cast<const double *>(base + off_arc);
     a.ang32 = reinterpret_cast<const float *>(base + off_a32);
+    a.grp = reinterpret_cast<const double *>(base + off_grp);
+    a.n_grp = grouped ? gf::group_count(quad->n_angular, quad->angular_rule) : 0;
+    a.grp_mid = gf::group_has_middle(quad->angular_rule);
     a.wmid = wmid;
 
     // Taylor coefficients of the subtraction at mu^2 (FP64, real axis), once per plan

@@ -24,15 +24,20 @@ constexpr double kRSlope = 0.45;
 // Everything a scan kernel needs, passed by value.
 struct ScanArgs {
     // Device tables:
-    //   rad: r[n_r], sqrt_r[n_r], g[n_r]   (y nodes of GL in log(1+y), dy r^{(D-2)/2}
+    //   rad: r[n_r], 1/r[n_r], g[n_r]      (y nodes of GL in log(1+y), dy r^{(D-2)/2}
     //                                       weights), FP64
     //   ang: (z^2, 2w, 2w z^2) for the n_a/2 symmetric pairs of the angular rule, FP64
     //   arc: xi[n_arc], w[n_arc]           (GL on [-1, 1]), FP64
     //   ang32: the pair table rounded to FP32
+    //   grp: the pairs (and an odd rule's middle node) in n_grp groups of
+    //        kGroupNodes, each as one rational function (group_table), FP64
     const double *rad;
     const double *ang;
     const double *arc;
     const float *ang32;
+    const double *grp;
+    int n_grp;    // 0: this rule's sums run over the pairs one by one
+    int grp_mid;  // a second table, about the middle of (0, 1), follows the first
     int n_r, n_a, n_arc;
     double wmid;  // weight of the middle node z = 0 (odd n_a), else 0
 
@@ -107,21 +112,35 @@ hipError_t launch_jmu(const ScanArgs &a, double mu2, double *dst, hipStream_t s)
 hipError_t launch_jmu_batch(ScanArgs *reqs, const ScanArgs *staged, const int *slots,
                             const double *mu2, int n, hipStream_t s);
 
+// Form of the angular sums a kernel runs: FP64 over pairs, FP32C, FP64 over the
+// rule's groups.
+enum : int { kPairs = 0, kFp32c = 1, kGroups = 2 };
+int scan_form(const ScanArgs &a, int precision);
+
+using ScanKernel = void (*)(ScanArgs);
+using ServeKernel = void (*)(const ScanArgs *, const WorkItem *, int, unsigned *);
+ScanKernel scan_kernel_groups(int lanes, bool taylor, bool split, bool poles);
+ScanKernel scan_kernel_pairs(int lanes, bool taylor, bool split, bool poles);
+ScanKernel scan_kernel_fp32c(int lanes, bool taylor, bool split, bool poles);
+ServeKernel serve_kernel_groups(bool split, bool poles);
+ServeKernel serve_kernel_pairs(bool split, bool poles);
+ServeKernel serve_kernel_fp32c(bool split, bool poles);
+
 // Persistent launch of `waves` wavefronts over n_items work items (device
-// arrays); *counter must be 0 on entry.  All items share precision, lanes,
-// the split flag of the radial rule and the pole-sum flag.
+// arrays), one lane per point; *counter must be 0 on entry.  All items share
+// the form, the split flag of the radial rule and the pole-sum flag.
 hipError_t launch_serve(const ScanArgs *reqs, const WorkItem *items, int n_items,
-                        unsigned *counter, int precision, int lanes, int split, int poles,
-                        int waves, hipStream_t s);
+                        unsigned *counter, int form, bool split, bool poles, int waves,
+                        hipStream_t s);
 
 // Wavefronts of that group's persistent kernel the current device holds at
 // once (occupancy x compute units x 4 waves per 256-thread block); 4096 if
 // the runtime cannot say.
-int serve_resident_waves(int precision, int lanes, int split, int poles);
+int serve_resident_waves(int form, bool split, bool poles);
 // Wavefronts of the scan kernel for these flags the current device holds at
 // once (occupancy x compute units; one wave per workgroup), cached per device
 // and kernel form; 4096 if the runtime cannot say.
-int scan_resident_waves(int precision, int lanes, bool taylor, bool split, bool poles);
+int scan_resident_waves(int form, int lanes, bool taylor, bool split, bool poles);
 
 // ---- host helpers shared by plans and the server (gf_host.cpp) ----------
 
@@ -131,10 +150,18 @@ int hip_fail(hipError_t e, const char *what);
 const char *last_error();
 
 void gauss_legendre(int n, std::vector<double> &x, std::vector<double> &w);
-// radial table [r | sqrt r | W], angular pair tables, arc table [xi | w]
+// radial table [r | 1/r | W], angular pair tables, arc table [xi | w]
 void radial_table(int n_r, double lambda2, int dim, int split, std::vector<double> &rad);
 void angular_tables(int n_a, int rule, int dim, std::vector<double> &ang,
                     std::vector<float> &ang32, double *wmid);
+// Groups the angular sums of this rule run in (0: pair by pair), whether they
+// have a second table, the doubles of both, and their coefficients from the
+// pair table and middle weight.
+int group_count(int n_a, int rule);
+inline bool group_has_middle(int rule) { return rule != GF_ANG_TANH_SINH; }
+size_t group_doubles(int n_a, int rule);
+void group_table(int n_a, int rule, const std::vector<double> &ang, double wmid,
+                 std::vector<double> &grp);
 void arc_table(int n_arc, std::vector<double> &arc);
 // masses, cutoff, scale and contour geometry of a (params, quadrature)
 void fill_constants(ScanArgs &a, const gf_params &p, const gf_propagators *props,
@@ -152,6 +179,12 @@ int set_grid(ScanArgs &a, const gf_grid &g, int lanes);
 void set_tail(ScanArgs &a, const gf_grid &g, int precision, int lanes);
 int current_device(int *dev);
 size_t align256(size_t b);
+
+// Folded nodes per group of the grouped angular sum, and doubles per group: the
+// denominator's coefficients a0..a7 below its leading 1, the numerator's
+// n0..n6 below its leading 1, and the numerator's scale.
+constexpr int kGroupNodes = 8;
+constexpr int kGroupDoubles = 2 * kGroupNodes;
 
 // Lanes per point of the tail of a one-lane scan.
 constexpr int kTailLanes = 16;

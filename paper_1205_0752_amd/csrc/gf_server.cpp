@@ -3,7 +3,7 @@
 // Requests are admitted in FIFO order against a device-memory arena (outputs
 // and node tables) and a slot table.  A scheduler thread repeatedly packs wave
 // tiles of every running request into persistent kernel launches (one per
-// precision x lanes-per-point group), giving each running request a fair share
+// form of the angular sums, radial rule and propagators), giving each running request a fair share
 // of the batch's evaluation budget.  Within a launch the most expensive tiles
 // are handed out first, so the launch ends on short ones.  A batch's staging
 // copy, table uploads and subtraction sums run on a prologue stream; its
@@ -102,6 +102,10 @@ struct Table {
     bool uploaded = false;
     double wmid = 0.0;       // angular tables: middle-node weight
     size_t off32 = 0;        // angular tables: offset of the FP32 pair table
+    // angular tables: the groups' coefficients, a range of the group arena (empty
+    // for a rule whose sums run pair by pair)
+    size_t grp_off = 0;
+    std::vector<char> grp_host;
 };
 
 struct Request {
@@ -116,6 +120,7 @@ struct Request {
     size_t out_off = 0, out_bytes = 0;
     std::string keys[3];  // radial, angular, arc table keys
     int lanes = 1;
+    int form = 0;  // of the angular sums (gf::scan_form)
     long long n_tiles = 0, next_tile = 0, tiles_done = 0;
     double cost_per_tile = 0.0;
     Clock::time_point t_submit, t_done;
@@ -138,9 +143,11 @@ struct Stage {
     }
 };
 
-// A table upload staged in this iteration: stage offset -> arena offset.
+// A table upload staged in this iteration: stage offset -> device address.
 struct Upload {
-    size_t stage_off, arena_off, bytes;
+    size_t stage_off;
+    char *dst;
+    size_t bytes;
 };
 
 struct Batch {
@@ -153,9 +160,13 @@ struct Batch {
 constexpr int kMaxInflight = 3;
 constexpr int kStages = kMaxInflight + 1;  // one per batch in flight + the one being filled
 constexpr int kComputeStreams = 2;
-constexpr int kMaxGroups = 8;  // precision x split x pole sums (one lanes value)
+constexpr int kMaxGroups = 9;  // form x (plain, split, pole sums)
 constexpr size_t kStageBytes = 32u << 20;
 constexpr long long kMaxItemsPerBatch = 1 << 20;
+// The angular tables' group coefficients live beside the budgeted arena (like
+// the staging buffers), so that the budget admits what it admitted by outputs
+// and node tables alone: 32 bytes per folded node, 128 KiB for the largest rule.
+constexpr size_t kGroupArenaBytes = 4u << 20;
 constexpr int kMaxNewPerBatch = 256;
 
 }  // namespace
@@ -167,12 +178,14 @@ struct gf_server {
     hipStream_t comp[kComputeStreams] = {};  // persistent serve launches, in turn
     int next_comp = 0;
     hipEvent_t group_ev[kStages][kMaxGroups] = {};
-    std::map<std::tuple<int, int, int, int>, int> resident;  // waves per launch group
+    std::map<std::tuple<int, int, int>, int> resident;  // waves per launch group
     // items a batch takes at least while tiles remain: between fill_min and
     // fill_max, half the tiles still to run
     long long fill_min = 0, fill_max = 0;
     char *d_arena = nullptr;
     Arena arena;
+    char *d_groups = nullptr;
+    Arena groups_arena;
     gf::ScanArgs *d_args = nullptr;
     double *d_jmu = nullptr;
     Stage stage[kStages];
@@ -206,6 +219,7 @@ struct gf_server {
     bool admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
                    std::vector<Upload> &uploads);
     Table *ensure_table(const std::string &key, const Request &r, bool *fits);
+    void evict_tables();
     void finish(Request *r);
     int fail_worker(hipError_t e, const char *what);
 };
@@ -228,7 +242,7 @@ std::string key_angular(const gf_quadrature &q, const gf_params &p)
 std::string key_arc(const gf_quadrature &q) { return "c" + std::to_string(q.n_arc); }
 
 // Arena bytes of a request's three node tables, as ensure_table builds them:
-// radial [r | sqrt r | W] (3 n_r doubles), angular pairs in FP64 then FP32
+// radial [r | 1/r | W] (3 n_r doubles), angular pairs in FP64 then FP32
 // (3 max(n_a/2, 1) each), arc [xi | w] (2 n_arc doubles); each range is
 // rounded up to the arena's 256-byte granule.
 size_t table_bytes(const gf_quadrature &q)
@@ -257,6 +271,21 @@ int gf_server::fail_worker(hipError_t e, const char *what)
     return GF_EDEVICE;
 }
 
+// Returns the ranges of every unreferenced table.  Called with the lock held.
+void gf_server::evict_tables()
+{
+    for (auto jt = tables.begin(); jt != tables.end();) {
+        if (jt->second.refs == 0) {
+            arena.release(jt->second.off, jt->second.bytes);
+            if (!jt->second.grp_host.empty())
+                groups_arena.release(jt->second.grp_off, jt->second.grp_host.size());
+            jt = tables.erase(jt);
+        } else {
+            ++jt;
+        }
+    }
+}
+
 // Builds (or finds) a table in the arena; *fits = false if it cannot be
 // placed now.  Called with the lock held.
 Table *gf_server::ensure_table(const std::string &key, const Request &r, bool *fits)
@@ -276,11 +305,15 @@ Table *gf_server::ensure_table(const std::string &key, const Request &r, bool *f
         std::vector<float> ang32;
         gf::angular_tables(r.q.n_angular, r.q.angular_rule, r.p.dimension == 0 ? 4 : r.p.dimension,
                            ang, ang32, &t.wmid);
+        std::vector<double> grp;
+        gf::group_table(r.q.n_angular, r.q.angular_rule, ang, t.wmid, grp);
         const size_t b64 = gf::align256(ang.size() * sizeof(double));
         t.host.assign(b64 + ang32.size() * sizeof(float), 0);
         std::memcpy(t.host.data(), ang.data(), ang.size() * sizeof(double));
         std::memcpy(t.host.data() + b64, ang32.data(), ang32.size() * sizeof(float));
         t.off32 = b64;
+        t.grp_host.resize(grp.size() * sizeof(double));
+        if (!grp.empty()) std::memcpy(t.grp_host.data(), grp.data(), t.grp_host.size());
     } else {
         std::vector<double> arc;
         gf::arc_table(r.q.n_arc, arc);
@@ -288,17 +321,15 @@ Table *gf_server::ensure_table(const std::string &key, const Request &r, bool *f
         std::memcpy(t.host.data(), arc.data(), t.host.size());
     }
     t.bytes = t.host.size();
-    if (!arena.alloc(t.bytes, &t.off)) {
-        // evict unreferenced tables and retry once
-        for (auto jt = tables.begin(); jt != tables.end();) {
-            if (jt->second.refs == 0) {
-                arena.release(jt->second.off, jt->second.bytes);
-                jt = tables.erase(jt);
-            } else {
-                ++jt;
-            }
-        }
-        if (!arena.alloc(t.bytes, &t.off)) {
+    auto place = [&] {
+        if (!arena.alloc(t.bytes, &t.off)) return false;
+        if (t.grp_host.empty() || groups_arena.alloc(t.grp_host.size(), &t.grp_off)) return true;
+        arena.release(t.off, t.bytes);
+        return false;
+    };
+    if (!place()) {
+        evict_tables();
+        if (!place()) {
             *fits = false;
             return nullptr;
         }
@@ -315,14 +346,7 @@ bool gf_server::admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
     if (free_slots.empty()) return false;
     size_t out_off;
     if (!arena.alloc(r->out_bytes, &out_off)) {
-        for (auto jt = tables.begin(); jt != tables.end();) {
-            if (jt->second.refs == 0) {
-                arena.release(jt->second.off, jt->second.bytes);
-                jt = tables.erase(jt);
-            } else {
-                ++jt;
-            }
-        }
+        evict_tables();
         if (!arena.alloc(r->out_bytes, &out_off)) return false;
     }
     // Each table is pinned (refs raised) as soon as it is found or built, so
@@ -344,14 +368,20 @@ bool gf_server::admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
     // any is marked uploaded, so a failed admission stages nothing
     size_t need = st.used;
     for (int k = 0; k < 3; ++k)
-        if (!tb[k]->uploaded) need = gf::align256(need) + tb[k]->bytes;
+        if (!tb[k]->uploaded)
+            need = gf::align256(gf::align256(need) + tb[k]->bytes) + tb[k]->grp_host.size();
     if (need > st.bytes) return undo(3);
     for (int k = 0; k < 3; ++k) {
         if (tb[k]->uploaded) continue;
         size_t doff;
         void *h = st.bump(tb[k]->bytes, &doff);
         std::memcpy(h, tb[k]->host.data(), tb[k]->bytes);
-        uploads.push_back(Upload{doff, tb[k]->off, tb[k]->bytes});
+        uploads.push_back(Upload{doff, d_arena + tb[k]->off, tb[k]->bytes});
+        if (!tb[k]->grp_host.empty()) {
+            h = st.bump(tb[k]->grp_host.size(), &doff);
+            std::memcpy(h, tb[k]->grp_host.data(), tb[k]->grp_host.size());
+            uploads.push_back(Upload{doff, d_groups + tb[k]->grp_off, tb[k]->grp_host.size()});
+        }
         tb[k]->uploaded = true;
     }
     r->out_off = out_off;
@@ -362,6 +392,10 @@ bool gf_server::admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
     a.rad = reinterpret_cast<const double *>(d_arena + tb[0]->off);
     a.ang = reinterpret_cast<const double *>(d_arena + tb[1]->off);
     a.ang32 = reinterpret_cast<const float *>(d_arena + tb[1]->off + tb[1]->off32);
+    a.grp = reinterpret_cast<const double *>(d_groups + tb[1]->grp_off);
+    a.n_grp = r->q.precision == GF_PREC_FP64
+                  ? gf::group_count(r->q.n_angular, r->q.angular_rule) : 0;
+    a.grp_mid = gf::group_has_middle(r->q.angular_rule);
     a.wmid = tb[1]->wmid;
     a.arc = reinterpret_cast<const double *>(d_arena + tb[2]->off);
     a.jmu = d_jmu + 2 * (GF_MAX_TAYLOR + 1) * (size_t)r->slot;
@@ -371,6 +405,7 @@ bool gf_server::admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
     a.out = reinterpret_cast<double *>(d_arena + out_off);
     a.cls = nullptr;
     r->n_tiles = a.n_tiles;
+    r->form = gf::scan_form(a, r->q.precision);
     r->state = GF_REQ_RUNNING;
     fresh.push_back(r);
     return true;
@@ -401,11 +436,11 @@ void gf_server::run()
         Batch b;
         std::vector<Request *> fresh;
         std::vector<Upload> uploads;
-        // launch groups: (precision, lanes per point, split radial rule, pole sums)
+        // launch groups: (form of the angular sums, split radial rule, pole sums)
         // -> runs of consecutive tiles (request, first tile, count)
-        std::map<std::tuple<int, int, int, int>, std::vector<std::tuple<Request *, long long, long long>>>
+        std::map<std::tuple<int, int, int>, std::vector<std::tuple<Request *, long long, long long>>>
             runs;
-        std::map<std::tuple<int, int, int, int>, std::vector<gf::WorkItem>> groups;
+        std::map<std::tuple<int, int, int>, std::vector<gf::WorkItem>> groups;
         Stage &st = stage[next_stage];
         {
             std::unique_lock<std::mutex> lock(mu);
@@ -467,7 +502,7 @@ void gf_server::run()
                         k = std::max(1LL, std::min(k, left));
                         k = std::min(k, kMaxItemsPerBatch - b.items);
                         if (k <= 0) break;
-                        runs[{r->q.precision, r->lanes, r->q.radial_split, r->has_props ? 1 : 0}]
+                        runs[{r->form, r->q.radial_split, r->has_props ? 1 : 0}]
                             .emplace_back(r, r->next_tile, k);
                         r->next_tile += k;
                         b.tiles.emplace_back(r, k);
@@ -483,7 +518,7 @@ void gf_server::run()
                     if (b.items >= fill_items) break;
                     const long long k = std::min(r->n_tiles - r->next_tile, fill_items - b.items);
                     if (k <= 0) continue;
-                    runs[{r->q.precision, r->lanes, r->q.radial_split, r->has_props ? 1 : 0}]
+                    runs[{r->form, r->q.radial_split, r->has_props ? 1 : 0}]
                         .emplace_back(r, r->next_tile, k);
                     r->next_tile += k;
                     b.tiles.emplace_back(r, k);
@@ -546,8 +581,8 @@ void gf_server::run()
 
             e = hipMemcpyAsync(st.d, st.h, st.used, hipMemcpyHostToDevice, stream);
             for (size_t k = 0; e == hipSuccess && k < uploads.size(); ++k)
-                e = hipMemcpyAsync(d_arena + uploads[k].arena_off, st.d + uploads[k].stage_off,
-                                   uploads[k].bytes, hipMemcpyDeviceToDevice, stream);
+                e = hipMemcpyAsync(uploads[k].dst, st.d + uploads[k].stage_off, uploads[k].bytes,
+                                   hipMemcpyDeviceToDevice, stream);
             if (e == hipSuccess && !fresh.empty())
                 e = gf::launch_jmu_batch(d_args, reinterpret_cast<const gf::ScanArgs *>(st.d + off_args),
                                          reinterpret_cast<const int *>(st.d + off_slots),
@@ -563,7 +598,7 @@ void gf_server::run()
                     rit = resident
                               .emplace(kv.first, gf::serve_resident_waves(
                                                      std::get<0>(kv.first), std::get<1>(kv.first),
-                                                     std::get<2>(kv.first), std::get<3>(kv.first)))
+                                                     std::get<2>(kv.first)))
                               .first;
                 const int waves = std::min(n, rit->second);
                 hipStream_t cs = comp[next_comp];
@@ -574,7 +609,7 @@ void gf_server::run()
                                          reinterpret_cast<const gf::WorkItem *>(st.d + off_items[gi]),
                                          n, reinterpret_cast<unsigned *>(st.d + off_cnt) + gi,
                                          std::get<0>(kv.first), std::get<1>(kv.first),
-                                         std::get<2>(kv.first), std::get<3>(kv.first), waves, cs);
+                                         std::get<2>(kv.first), waves, cs);
                 if (e == hipSuccess) e = hipEventRecord(group_ev[next_stage][gi], cs);
                 if (e == hipSuccess) b.ev.push_back(group_ev[next_stage][gi]);
                 ++gi;
@@ -652,6 +687,7 @@ int gf_server_create(const gf_server_config *cfg, gf_server_t **out)
     for (int k = 0; e == hipSuccess && k < kComputeStreams; ++k)
         e = hipStreamCreateWithFlags(&s->comp[k], hipStreamNonBlocking);
     if (e == hipSuccess) e = hipMalloc(&s->d_arena, cfg->device_budget_bytes);
+    if (e == hipSuccess) e = hipMalloc(&s->d_groups, kGroupArenaBytes);
     if (e == hipSuccess) e = hipMalloc(&s->d_args, sizeof(gf::ScanArgs) * cfg->max_inflight);
     if (e == hipSuccess)
         e = hipMalloc(&s->d_jmu, 2 * sizeof(double) * (GF_MAX_TAYLOR + 1) * cfg->max_inflight);
@@ -668,11 +704,12 @@ int gf_server_create(const gf_server_config *cfg, gf_server_t **out)
         gf_server_destroy(s);
         return r;
     }
-    const long long waves = std::max(gf::serve_resident_waves(0, 1, 0, 0),
-                                     gf::serve_resident_waves(1, 1, 0, 0));
+    const long long waves = std::max(gf::serve_resident_waves(gf::kGroups, false, false),
+                                     gf::serve_resident_waves(gf::kFp32c, false, false));
     s->fill_min = std::min<long long>(3 * waves / 2, kMaxItemsPerBatch);
     s->fill_max = std::min<long long>(6 * waves, kMaxItemsPerBatch);
     s->arena.init(cfg->device_budget_bytes);
+    s->groups_arena.init(kGroupArenaBytes);
     for (int k = cfg->max_inflight - 1; k >= 0; --k) s->free_slots.push_back(k);
     s->worker = std::thread([s] { s->run(); });
     *out = s;
@@ -916,6 +953,7 @@ int gf_server_destroy(gf_server_t *s)
     if (s->d_jmu) (void)hipFree(s->d_jmu);
     if (s->d_args) (void)hipFree(s->d_args);
     if (s->d_arena) (void)hipFree(s->d_arena);
+    if (s->d_groups) (void)hipFree(s->d_groups);
     if (s->stream) (void)hipStreamDestroy(s->stream);
     for (int k = 0; k < kComputeStreams; ++k)
         if (s->comp[k]) (void)hipStreamDestroy(s->comp[k]);

@@ -1,0 +1,77 @@
+"""The grouped angular sums (FP64): rules at the edges of the groups of eight
+folded nodes, against the oracle at the FP64 parity bar, and against the
+pair-by-pair form, which a unit numerator selects."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1205_0752_amd as gf
+from paper_1205_0752_amd.workloads import (GC1, GC2, GL, TANH_SINH, Grid, Params, Propagators,
+                                           Quadrature)
+from parity_bars import EPS, check_fp64
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+# ragged, across the cut, with real-axis points left of x = 0
+GRID = Grid(29, 22, -9.0, 4.0, -3.1, 3.3)
+HEAVY = Params(3.5, 2.0, 1.5, 1e6)
+
+
+def _scan(p, q, lanes, props=None):
+    plan = gf.Plan(p, q, props)
+    cls = torch.empty((GRID.n_im, GRID.n_re), dtype=torch.int8, device="cuda")
+    g = gf.scan_plan(plan, GRID, cls=cls, lanes=lanes)
+    torch.cuda.synchronize()
+    plan.close()
+    return g.cpu().numpy().ravel(), cls.cpu().numpy().ravel()
+
+
+@pytest.mark.parametrize("rule,dim,n_a", [
+    (GC2, 4, 62), (GC2, 4, 63), (GC2, 4, 64),      # 31 + 0, 31 + 1 and 32 nodes: full and odd rule
+    (GC2, 4, 90), (GC2, 4, 96), (GC2, 4, 113),     # 45, 48 and 57 nodes: 6, 6 and 8 groups
+    (GC2, 4, 111), (GC1, 2, 64), (GL, 3, 95),      # 56: an odd count of groups
+    (TANH_SINH, 4, 62), (TANH_SINH, 4, 129), (GC2, 4, 512)])
+@pytest.mark.parametrize("lanes", [1, 16])
+def test_grouped_rules_match_the_oracle(rule, dim, n_a, lanes):
+    p = HEAVY if dim == 4 else Params(1.3, 0.6, 1.0, 1e6, 1.0, 0, dim)
+    q = Quadrature(40, n_a, 9, gf.FP64, rule)
+    g, c = _scan(p, q, lanes)
+    go, co, cond = oracle.scan(p, q, GRID, want_cond=True)
+    assert np.array_equal(c, co)
+    ok = co != oracle.SINGULAR
+    check_fp64(g[ok], go[ok], cond[ok])
+
+
+@pytest.mark.parametrize("props", [
+    ((1 + 0.8j, 0.5),), ((0.4, 1.0), (2.5, -0.3))], ids=["complex", "real"])
+@pytest.mark.parametrize("mu2", [0.0, 1.0])
+@pytest.mark.parametrize("rule,n_a", [(GC2, 64), (GL, 113), (TANH_SINH, 91)])
+def test_groups_equal_the_pairs(props, mu2, rule, n_a):
+    """N = 1 as a numerator runs the pair-by-pair sums; both forms differ by
+    rounding alone, each within the parity bar of the other's condition."""
+    p = Params(1.0, 1.0, mu2, 1e6)
+    q = Quadrature(48, n_a, 8, gf.FP64, rule)
+    legs = (props, ((1.0, 0.6), (3.0, 0.4)))
+    a, ca = _scan(p, q, 4, Propagators(*legs))
+    b, cb = _scan(p, q, 4, Propagators(*legs, ((0, 0, 1.0),)))
+    x = oracle.grid_points(GRID)
+    _, _, cond = oracle.eval_points(p, q, x, want_cond=True, props=Propagators(*legs))
+    same = (ca == cb) & (ca != oracle.SINGULAR)
+    # a real numerator keeps the mirror class only where the legs do; both exist here
+    assert same.mean() > 0.9
+    err = np.abs(a - b)[same]
+    assert np.all(err <= 2 * 64 * EPS * cond[same] * np.abs(b[same]) + 1e-15)
+
+
+def test_large_and_tiny_magnitudes_leave_the_groups():
+    """|U^2 / V^2| beyond the groups' range (a point next to x = 0, and a cutoff
+    of 1e20) runs over the pairs."""
+    p, q = Params(1.0, 1.0, 1.0, 1e20), Quadrature(64, 96, 16)
+    grid = Grid(3, 3, -3e-9, 3e-9, -3e-9, 3e-9)
+    plan = gf.Plan(p, q)
+    g = gf.scan_plan(plan, grid).cpu().numpy().ravel()
+    plan.close()
+    go, co, cond = oracle.scan(p, q, grid, want_cond=True)
+    check_fp64(g, go, cond)
