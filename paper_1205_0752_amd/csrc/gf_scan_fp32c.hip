@@ -4,16 +4,26 @@
 namespace gf {
 namespace {
 
-// Six waves per SIMD (measured; the few spills sit outside the inner loop).
+// Waves per SIMD the registers are budgeted for.  At few lanes per point the
+// plain form's inner loop runs best at six, its spills outside it (1024^2 at 512
+// x 256 nodes, two lanes: 11.51 ms at six, 11.68 at five).  Elsewhere the spills
+// cost more than two waves hide: the forms with more per node (512^2 at 256 x
+// 128: pole sums 2.67 -> 2.09 ms at four, with a numerator 5.10 -> 2.96; 1024^2
+// split rule 5.45 -> 4.37), and many lanes per point, where a wave is mostly set-up
+// (200 x 150 at 64 x 64: 50.6 -> 43.3 us; 8 lanes, 600 x 400 at 400 x 400: 3.49 ms at
+// six, 3.65 at four).
+template <int L, bool SPLIT, bool POLES>
+constexpr int kWaves = POLES || SPLIT || L >= 16 ? 4 : 6;
+
 template <int L, bool TAYLOR, bool SPLIT, bool POLES>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6)))
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<L, SPLIT, POLES>)))
 scan_kernel_fp32c(ScanArgs a)
 {
     scan_body<kFp32c, L, TAYLOR, SPLIT, POLES>(a);
 }
 
 template <bool SPLIT, bool POLES>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<1, SPLIT, POLES>)))
 serve_kernel_fp32c(const ScanArgs *__restrict__ reqs, const WorkItem *__restrict__ items, int n_items,
         unsigned *counter)
 {
