@@ -91,44 +91,123 @@ __device__ void cut_bisect(CutWalk &w, double lo, double hi, bool lo_pos)
     if (zc.r >= 0.0 && zc.r <= 1.0) w.hit = true;
 }
 
-// The walks below take their samples in chunks of 64 from a fresh anchor,
-// eight samples at a time, each group's first sample carried over from the
-// one before as one more step of the same recurrence.  The eight signs are
-// compared with one branch per group (sign changes are rare: at most one per
-// real-segment walk on the bench box); inside it a loop kept rolled bisects
-// each change in order, so a walk holds one copy of the bisection.  The
-// comparison starts from the sign of the walk's first sample, which has no
-// predecessor; only a walk's last group can reach past its last sample
-// (k + j >= k_end: those signs are not compared, and nothing reads them after
-// it).  Once every point of
-// the wave has met the cut, the rest of the part cannot change the map: the
-// wave leaves the part at the next chunk (wave-uniform).  Positions, signs,
-// brackets and their order are those of a one-sample-at-a-time walk.
-constexpr int kGroup = 8;
+// Which samples a walk has to look at.  Im zeta changes sign with
+//   straight part  f(e) = Im((x1 + dir e)^2 conj(4 x dir)),  a quadratic in e = e^u - 1,
+//   arc            f(psi) = alpha + b_c cos psi + b_s sin psi,
+// and the sign a sample computes is f's wherever |f| exceeds a bound B on all
+// rounding of the sample: its position (a recurrence, re-anchored every 64
+// samples, within 128 eps) and its value.  f = B and f = -B have at most four
+// roots on a part, taken in closed form; between two of them f is either
+// beyond B throughout, and every sample there has the same sign, or within it
+// (no more than a few ulp wide at a simple zero, a whole part where f vanishes
+// identically).  So a walk computes the signs of the samples next to each root,
+// two to either side for the roots' own rounding, and of those between two
+// roots where f is within B; the map is the one that all samples give.
+//
+// The map is bound by that per-point set-up (logarithms, arc cosines and the
+// bisections' exponentials) instead of n samples a part.  1024^2 points, 4096
+// samples a part: 3.5 ms when every sample was computed (7 to 10 VALU
+// instructions each, VALU-bound), 0.09 ms now; of that step 0.17 ms came from
+// the roots and the rest from settling most bisections by the roots (cut_settled).
+constexpr double kSampleTol = 1e-13;  // of the terms' magnitudes
+constexpr int kPad = 2;
 
-__device__ __forceinline__ bool group_changes(bool prev, const bool (&p)[kGroup], int k, int k_end)
+// Root positions in units of samples, ascending (unused ones beyond any sample).
+struct Roots {
+    double k[4];
+};
+
+constexpr double kNoRoot = 1e18;
+
+__device__ __forceinline__ void sort_roots(Roots &r)
 {
-    bool any = p[0] != prev;
-#pragma unroll
-    for (int j = 1; j < kGroup; ++j) any |= (k + j < k_end) & (p[j] != p[j - 1]);  // no short cut
-    return any;
+    auto order = [&](int a, int b) {
+        const double lo = fmin(r.k[a], r.k[b]), hi = fmax(r.k[a], r.k[b]);
+        r.k[a] = lo;
+        r.k[b] = hi;
+    };
+    order(0, 1);
+    order(2, 3);
+    order(0, 2);
+    order(1, 3);
+    order(1, 2);
 }
 
-__device__ __forceinline__ void group_bisect(CutWalk &w, bool prev, const bool (&p)[kGroup], int k,
-                                             int k_end, double step, double base)
+// Visits the samples first..n-1 that the roots leave undecided, in ascending
+// order, each next to its predecessor: visit(k, fresh) computes sample k's
+// sign, comparing it with sample k-1's unless fresh.  inside(t) says whether f
+// lies within its bound at position t.  ends: also the part's first and last
+// samples.
+template <class Inside, class Visit>
+__device__ __forceinline__ void visit_undecided(const Roots &r, int first, int n, bool ends,
+                                                Inside inside, Visit visit)
 {
+    const double end = (double)(n - 1);
+    int last = first - 1;  // last sample visited
+    auto window = [&](int lo, int hi) {
+        lo = max(lo, last + 1);
+        hi = min(hi, n - 1);
+        if (lo > hi) return;
+        const bool fresh = last < first || lo > last + 1;
+        int k = fresh ? max(lo - 1, first) : lo;
+        for (bool f = fresh; k <= hi; ++k, f = false) visit(k, f);
+        last = hi;
+    };
 #pragma unroll 1
-    for (int j = 0; j < kGroup && k + j < k_end; ++j) {
-        bool a = prev, b = p[0];
+    for (int i = 0; i <= 4; ++i) {
+        double a = (double)first, b = kNoRoot;
 #pragma unroll
-        for (int i = 1; i < kGroup; ++i)  // p[j - 1], p[j] without indexing registers dynamically
-            if (i == j) {
-                a = p[i - 1];
-                b = p[i];
-            }
-        if (b != a)
-            cut_bisect(w, fma((double)(k + j - 1), step, base), fma((double)(k + j), step, base), a);
+        for (int q = 0; q < 4; ++q) {  // r.k[i - 1], r.k[i] without indexing registers dynamically
+            if (q == i - 1) a = r.k[q];
+            if (q == i) b = r.k[q];
+        }
+        if (a > end + (kPad + 1)) break;
+        int lo = i == 0 ? first : (int)fmax(a, (double)first) - kPad;
+        int hi = i == 0 ? (ends ? first + kPad + 1 : first - 1) : (int)fmin(a, end) + kPad + 1;
+        // two roots this close have touching windows
+        const bool covered = i > 0 && b <= a + 2 * kPad && b < end;
+        b = fmin(b, end);
+        if (!covered && b > a && inside(0.5 * (a + b))) hi = (int)b + kPad + 1;
+        window(lo, hi);
     }
+    if (ends) window(n - 2 - kPad, n - 1);
+}
+
+// A sign change of a straight part between samples k-1 and k.  Where the two
+// roots f = +-B about it stand alone and close together, the bisection ends
+// between them: Re zeta there is known to the difference of its values at the
+// two, and only a value next to 0 or 1 needs the bisection itself (forty
+// exponentials and divisions).  Returns whether it was settled so.
+__device__ __forceinline__ bool cut_settled(CutWalk &w, const Roots &r, double h, int k)
+{
+    int n = 0;
+    double a = 0.0, b = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (r.k[q] > k - 1.5 && r.k[q] < k + 0.5) {
+            a = n == 0 ? r.k[q] : a;
+            b = r.k[q];
+            ++n;
+        }
+    if (n != 2 || !(a > k - 1 && b < k && b - a < 1e-6)) return false;
+    const double za = cut_zeta(w, a * h).r, zb = cut_zeta(w, b * h).r;
+    const double lo = fmin(za, zb), hi = fmax(za, zb);
+    if (!(hi - lo < 1e-7)) return false;
+    if (lo > 1e-6 && hi < 1.0 - 1e-6) {
+        w.hit = true;
+        return true;
+    }
+    return hi < -1e-6 || lo > 1.0 + 1e-6;
+}
+
+// Real roots of q2 e^2 + q1 e + q0 (cancellation-free; NaN where there is none).
+__device__ __forceinline__ void quadratic_roots(double q2, double q1, double q0, double &r1,
+                                                double &r2)
+{
+    const double d = sqrt(fma(q1, q1, -4.0 * (q2 * q0)));
+    const double t = -0.5 * (q1 + copysign(d, q1));
+    r1 = t / q2;
+    r2 = q0 / t;
 }
 
 // Samples along the straight part, y_k = dir e_k, e_k = e^{u_k} - 1, u_k = k h,
@@ -142,33 +221,64 @@ __device__ __forceinline__ void group_bisect(CutWalk &w, bool prev, const bool (
 template <bool REAL>
 __device__ void cut_walk_straight(CutWalk &w, int n, double T)
 {
+    if (w.hit) return;
     const double h = T / (n - 1);
     const double c = expm1(h);
     const cd c4 = cmul(w.x4, w.dir);
     const double c4r2 = 2.0 * c4.r;
-    auto pos_at = [&](double e) {
+    auto value_at = [&](double e) {
         const double ur = fma(w.dir.r, e, w.x1.r);
         const double ui = REAL ? w.x1.i : fma(w.dir.i, e, w.x1.i);
-        return fma(ur, fma(ui, c4r2, -(ur * c4.i)), ui * (ui * c4.i)) > 0.0;
+        return fma(ur, fma(ui, c4r2, -(ur * c4.i)), ui * (ui * c4.i));
     };
-    bool prev = pos_at(expm1(h));  // the first sample, k = 1
-    for (int k0 = 1; k0 < n; k0 += 64) {
-        if (__all(w.hit)) break;
-        const int kend = min(k0 + 64, n);
-        double e0 = expm1(k0 * h);
-        for (int k = k0; k < kend; k += kGroup) {
-            double e[kGroup];
-            bool p[kGroup];
-            e[0] = e0;
-#pragma unroll
-            for (int j = 1; j < kGroup; ++j) e[j] = fma(e[j - 1], c, e[j - 1] + c);
-#pragma unroll
-            for (int j = 0; j < kGroup; ++j) p[j] = pos_at(e[j]);
-            if (group_changes(prev, p, k, kend)) group_bisect(w, prev, p, k, kend, h, 0.0);
-            prev = p[kGroup - 1];
-            e0 = fma(e[kGroup - 1], c, e[kGroup - 1] + c);
+    // f = q2 e^2 + q1 e + q0
+    const cd cc = mk(c4.r, -c4.i), d2 = cmul(w.dir, w.dir), xd = cmul(w.x1, w.dir),
+             x2 = cmul(w.x1, w.x1);
+    const double q2 = cmul(d2, cc).i, q1 = 2.0 * cmul(xd, cc).i, q0 = cmul(x2, cc).i;
+    if (q2 == 0.0 && q1 == 0.0 && q0 == 0.0) return;  // every sample's value is 0: no sign change
+    // B: tol times the terms' magnitudes, not |f|'s scale |4x| (|x1| + e)^2: next to the
+    // real axis every term carries the tiny Im x, and so does the rounding
+    const double xr = fabs(w.x1.r), xi = fabs(w.x1.i), dr = fabs(w.dir.r),
+                 di = REAL ? 0.0 : fabs(w.dir.i);
+    const double tr = kSampleTol * fabs(c4r2), ti = kSampleTol * fabs(c4.i);
+    const double b2 = fma(tr, dr * di, ti * fma(dr, dr, di * di));
+    const double b1 = fma(tr, fma(xr, di, xi * dr), 2.0 * ti * fma(xr, dr, xi * di));
+    const double b0 = fma(tr, xr * xi, ti * fma(xr, xr, xi * xi));
+    Roots r;
+    const double ih = 1.0 / h, top = w.lam2 * 1.01;
+    auto place = [&](double e) { return e > 0.0 && e < top ? log1p(e) * ih : kNoRoot; };
+    // two roots next to one another share the logarithm
+    auto place2 = [&](double ea, double eb, double &ka, double &kb) {
+        ka = place(ea);
+        const double d = (eb - ea) / (1.0 + ea);
+        kb = ka < kNoRoot && fabs(d) < 1e-8 ? fma(d, ih, ka) : place(eb);
+    };
+    double e0, e1, e2, e3;
+    quadratic_roots(q2 - b2, q1 - b1, q0 - b0, e0, e1);
+    quadratic_roots(q2 + b2, q1 + b1, q0 + b0, e2, e3);
+    place2(e0, e2, r.k[0], r.k[2]);
+    place2(e1, e3, r.k[1], r.k[3]);
+    sort_roots(r);
+    auto inside = [&](double t) {
+        const double e = expm1(t * h);
+        return fabs(fma(fma(q2, e, q1), e, q0)) <= fma(fma(b2, e, b1), e, b0);
+    };
+    int at = -1;  // the recurrence's sample
+    double e = 0.0;
+    bool prev = false;
+    visit_undecided(r, 1, n, false, inside, [&](int k, bool fresh) {
+        if (w.hit) return;
+        const int anchor = ((k - 1) & ~63) + 1;
+        if (at < anchor || at >= k) {
+            at = anchor;
+            e = expm1(anchor * h);
         }
-    }
+        for (; at < k; ++at) e = fma(e, c, e + c);
+        const bool p = value_at(e) > 0.0;
+        if (!fresh && p != prev && !cut_settled(w, r, h, k))
+            cut_bisect(w, fma((double)(k - 1), h, 0.0), fma((double)k, h, 0.0), prev);
+        prev = p;
+    });
 }
 
 // Samples along an arc from angle phi, psi_k = phi + span k/(n-1), k = 0..n-1
@@ -183,6 +293,7 @@ __device__ void cut_walk_straight(CutWalk &w, int n, double T)
 // so the rounding stays that of the direct product.
 __device__ void cut_walk_arc(CutWalk &w, int n, double phi, double span)
 {
+    if (w.hit) return;
     const double dpsi = span / (n - 1);
     double s, c;
     sincos(dpsi, &s, &c);
@@ -193,30 +304,51 @@ __device__ void cut_walk_arc(CutWalk &w, int n, double phi, double span)
     const cd B = cscale(cx4, l4);
     const double alpha = 2.0 * l2 * fma(cx4.r, w.x1.i, cx4.i * w.x1.r);
     const double bc = A.i + B.i, bs = B.r - A.r;
-    auto pos_at = [&](cd e) { return fma(bc, e.r, fma(bs, e.i, alpha)) > 0.0; };
-    bool prev;
-    {
-        sincos(fma(0.0, dpsi, phi), &s, &c);  // the first sample, k = 0, as the walk takes it
-        prev = pos_at(mk(c, s));
-    }
-    for (int k0 = 0; k0 < n; k0 += 64) {
-        if (__all(w.hit)) break;
-        const int kend = min(k0 + 64, n);
-        sincos(fma((double)k0, dpsi, phi), &s, &c);
-        cd e0 = mk(c, s);
-        for (int k = k0; k < kend; k += kGroup) {
-            cd e[kGroup];
-            bool p[kGroup];
-            e[0] = e0;
-#pragma unroll
-            for (int j = 1; j < kGroup; ++j) e[j] = cmul(e[j - 1], rot);
-#pragma unroll
-            for (int j = 0; j < kGroup; ++j) p[j] = pos_at(e[j]);
-            if (group_changes(prev, p, k, kend)) group_bisect(w, prev, p, k, kend, dpsi, phi);
-            prev = p[kGroup - 1];
-            e0 = cmul(e[kGroup - 1], rot);
+    if (alpha == 0.0 && bc == 0.0 && bs == 0.0) return;
+    const double bound = kSampleTol * (fabs(alpha) + fabs(bc) + fabs(bs));
+    // f = alpha + R cos(psi - psi0) = +-bound; on an arc of nearly a whole turn
+    // a root next to one end may come out at the other: both are visited
+    const double ir = 1.0 / hypot(bc, bs), psi0 = atan2(bs, bc), id = 1.0 / dpsi;
+    const double period = 2.0 * M_PI * fabs(id);
+    auto place = [&](double psi) {
+        double t = (psi - phi) * id;
+        t -= floor(t / period) * period;
+        return t > period - 2 * kPad ? t - period : t;  // just before the arc's start
+    };
+    const bool ends = period < n + 4 * kPad;
+    Roots r;
+    const double g0 = (-bound - alpha) * ir, g1 = (bound - alpha) * ir;
+    const double a0 = acos(fmin(fmax(g0, -1.0), 1.0)), a1 = acos(fmin(fmax(g1, -1.0), 1.0));
+    const bool has0 = fabs(g0) <= 1.0 + 1e-12, has1 = fabs(g1) <= 1.0 + 1e-12;
+    r.k[0] = has0 ? place(psi0 - a0) : kNoRoot;
+    r.k[1] = has0 ? place(psi0 + a0) : kNoRoot;
+    r.k[2] = has1 ? place(psi0 - a1) : kNoRoot;
+    r.k[3] = has1 ? place(psi0 + a1) : kNoRoot;
+    sort_roots(r);
+    auto inside = [&](double t) {
+        double sn, cs;
+        sincos(fma(t, dpsi, phi), &sn, &cs);
+        return fabs(fma(bc, cs, fma(bs, sn, alpha))) <= bound;
+    };
+    int at = -1;
+    cd e = mk(1.0, 0.0);
+    bool prev = false;
+    auto visit = [&](int k, bool fresh) {
+        if (w.hit) return;
+        const int anchor = k & ~63;
+        if (at < anchor || at >= k) {
+            at = anchor;
+            double sn, cs;
+            sincos(fma((double)anchor, dpsi, phi), &sn, &cs);
+            e = mk(cs, sn);
         }
-    }
+        for (; at < k; ++at) e = cmul(e, rot);
+        const bool p = fma(bc, e.r, fma(bs, e.i, alpha)) > 0.0;
+        if (!fresh && p != prev)
+            cut_bisect(w, fma((double)(k - 1), dpsi, phi), fma((double)k, dpsi, phi), prev);
+        prev = p;
+    };
+    visit_undecided(r, 0, n, ends, inside, visit);
 }
 
 __device__ CutWalk cut_walk_begin(const ScanArgs &a, double xr, double xi)
@@ -243,11 +375,10 @@ __device__ bool cut_hits_real_axis(const ScanArgs &a, double xr, double xi, int 
 // where the ray ends: psi = phi (1 - k/(n-1)), k = 0..n-1, back to 0 the
 // short way, or (the long way round) psi = phi + L k/(n-1),
 // L = sign(phi) 2 pi - phi.
-__device__ bool cut_hits_ray_arc(const ScanArgs &a, double xr, double xi, int n, double T,
-                                 bool long_way)
+__device__ bool cut_hits_ray_arc(const ScanArgs &a, double xr, double xi, double phi, int n,
+                                 double T, bool long_way)
 {
     CutWalk w = cut_walk_begin(a, xr, xi);
-    const double phi = atan2(xi, xr);
     double s, c;
     sincos(phi, &s, &c);
     w.dir = mk(c, s);
@@ -274,21 +405,23 @@ __global__ void __launch_bounds__(64) obstruction_kernel(ScanArgs a, int n, doub
     int sign = 0, info = 0;
     const PointArg pa = point_arg(xr, xi);
     int cls = classify(a, pa.v, pa.phi, &sign, &info);
-    double ei = xi;
+    double ei = xi, phi = pa.phi;
     int ecls = cls;
     if (cls == kMirror) {  // the scan evaluates the conjugate point, if it has a contour
         ecls = classify(a, pa.v, -pa.phi, &sign);
-        if (ecls == kMirror || ecls == kSingular || ecls == kLong)
+        if (ecls == kMirror || ecls == kSingular || ecls == kLong) {
             cls = ecls = (info & kInfoRValid) ? kR : kLong;
-        else
+        } else {
             ei = -xi;
+            phi = -phi;
+        }
     }
     int v = real_hit ? 1 : 0;
     if (cls == kSingular) {
         v |= 4;
     } else {
         const bool used_hit = ecls == kR ? (ei == xi ? real_hit : cut_hits_real_axis(a, xr, ei, n, T))
-                                         : cut_hits_ray_arc(a, xr, ei, n, T, ecls == kLong);
+                                         : cut_hits_ray_arc(a, xr, ei, phi, n, T, ecls == kLong);
         if (used_hit) v |= 2;
     }
     out[(size_t)ib * (size_t)a.n_re + (size_t)ia] = (uint8_t)v;
