@@ -106,6 +106,10 @@ hipError_t launch_obstruction(const ScanArgs &a, int n, double T, uint8_t *out, 
 // Computes the unscaled real-axis sum at x = mu^2 (FP64) into dst[0..1].
 hipError_t launch_jmu(const ScanArgs &a, double mu2, double *dst, hipStream_t s);
 
+// The same where the tables are generated on the device: also writes the
+// group tables (a.n_grp groups) from the pair table into grp.
+hipError_t launch_jmu_groups(const ScanArgs &a, double mu2, double *dst, double *grp, hipStream_t s);
+
 // The same for n requests at once (device pointers): copies staged[i] into
 // reqs[slots[i]] and writes request i's coefficients, at mu2[i], into the jmu
 // slot that staged[i] names.

@@ -64,8 +64,8 @@ __device__ void taylor_node(const Args &a, cd U0, double y, cd omega, int n, cd 
     }
 }
 
-// <1/(U - V z)> pair by pair from the direct denominators (where V^2 = 0 leaves the
-// groups no sigma, i.e. mu^2 = 0).
+// <1/(U - V z)> pair by pair from the direct denominators, each reciprocal with a
+// cubic step.
 template <class Args>
 __device__ cd pairs_one_by_one(const Args &a, cd U, cd V2)
 {
@@ -81,22 +81,32 @@ __device__ cd pairs_one_by_one(const Args &a, cd U, cd V2)
 }
 
 // Subtraction coefficients at the real point mu^2 on the real axis, by one
-// wavefront: K_0 = the subtraction sum of eq. 14 (the order-0 operator t^0),
+// block: K_0 = the subtraction sum of eq. 14 (the order-0 operator t^0),
 // and for t^n with n >= 1 the Taylor coefficients K_i = (1/i!) d^i/dx^i of the
 // same sum (eq. 13 about x = mu^2).
 //
 // Where the scan's sums run in groups (GROUPED) so do these, and like there every
 // reciprocal takes a cubic step: S and J are about ten times their difference
 // G, so a bias of either alone would show (the pair form's Newton steps bias
-// both alike).
-template <bool SPLIT, bool POLES, bool GROUPED, class Args>
-__device__ __forceinline__ void jmu_wave_impl(const Args &a, double mu2, double *dst, int lane)
+// both alike).  TABLES is false where the group tables are still being written
+// (jmu_groups_kernel): the sums then go pair by pair.
+//
+// A plan's sum is a few hundred nodes, bound by the latency of one node's chain.
+// THREADS = 64: one wave per request finds room between the blocks of scans that are
+// running (blocks of four waves waited 5 ms for it, 0.2 ms by one wave, behind
+// two serve kernels), and a plan computes J once.  THREADS = 256 where it is
+// computed on every call: a node per thread.
+template <bool SPLIT, bool POLES, bool GROUPED, bool TABLES, int THREADS, class Args>
+__device__ __forceinline__ void jmu_block_impl(const Args &a, double mu2, double *dst)
 {
+    constexpr int kWaves = THREADS / 64;
+    __shared__ double part[kWaves][2 * (GF_MAX_TAYLOR + 1)];
+    const int tid = threadIdx.x;
     const PointCtx pc = point_setup<SPLIT, POLES>(a, mu2, 0.0, mu2, 0.0, kR, 0, 0);
     double sr = 0.0, si = 0.0;
     cd acc[GF_MAX_TAYLOR + 1];
     for (int i = 0; i <= GF_MAX_TAYLOR; ++i) acc[i] = mk(0.0, 0.0);
-    for (int k = lane; k < pc.nodes; k += 64) {
+    for (int k = tid; k < pc.nodes; k += THREADS) {
         cd U, V2, w;
         node_coeffs<SPLIT, POLES>(a, pc, k, U, V2, w);
         cd N[3];
@@ -106,10 +116,15 @@ __device__ __forceinline__ void jmu_wave_impl(const Args &a, double mu2, double 
         if constexpr (GROUPED) {
             double r, g, rinv;
             radial_node<SPLIT>(a, pc, k, r, g, &rinv);
-            const cd iv = mk(rinv * rcp64c(4.0 * mu2), 0.0);
-            auto e0 = [&] { return mk((mu2 - r) * (mu2 - r) * iv.r, 0.0); };
-            A = angular_sum_grouped_p<POLES, false>(a, mk(mu2 + r, 0.0), iv, e0,
-                                             [&](cd Ua) { return pairs_one_by_one(a, Ua, V2); });
+            if constexpr (TABLES) {
+                const cd iv = mk(rinv * rcp64c(4.0 * mu2), 0.0);
+                auto e0 = [&] { return mk((mu2 - r) * (mu2 - r) * iv.r, 0.0); };
+                A = angular_sum_grouped_p<POLES, false>(
+                    a, mk(mu2 + r, 0.0), iv, e0, [&](cd Ua) { return pairs_one_by_one(a, Ua, V2); });
+            } else {
+                static_assert(TABLES || !POLES, "scans on device tables have single poles");
+                A = pairs_one_by_one(a, U, V2);
+            }
             if (!POLES) w = cscale(cinv(mk(r + a.m2_re, a.m2_im)), g);
         } else {
             A = angular_sum_p<0, POLES>(a, U, V2, ~0, num ? N : nullptr);
@@ -132,61 +147,114 @@ __device__ __forceinline__ void jmu_wave_impl(const Args &a, double mu2, double 
             }
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        sr += __shfl_xor(sr, off);
-        si += __shfl_xor(si, off);
-    }
-    for (int i = 1; i <= a.n_taylor; ++i) {
+    // each wave's sums, then the waves' in order (t^-1, no subtraction, leaves K_0 = 0)
+    acc[0] = a.n_taylor < 0 ? mk(0.0, 0.0) : mk(sr, si);
+    const int n = max(a.n_taylor, 0);
+    for (int i = 0; i <= n; ++i) {
         double ar = acc[i].r, ai = acc[i].i;
         for (int off = 32; off > 0; off >>= 1) {
             ar += __shfl_xor(ar, off);
             ai += __shfl_xor(ai, off);
         }
-        if (lane == 0) {
-            dst[2 * i] = ar;
-            dst[2 * i + 1] = ai;
+        if ((tid & 63) == 0) {
+            part[tid >> 6][2 * i] = ar;
+            part[tid >> 6][2 * i + 1] = ai;
         }
     }
-    if (lane == 0) {
-        // t^-1 (no subtraction) leaves K_0 = 0
-        dst[0] = a.n_taylor < 0 ? 0.0 : sr;
-        dst[1] = a.n_taylor < 0 ? 0.0 : si;
+    __syncthreads();
+    if (tid < 2 * (n + 1)) {
+        double v = 0.0;
+        for (int w = 0; w < kWaves; ++w) v += part[w][tid];
+        dst[tid] = v;
     }
 }
 
 template <bool GROUPED, class Args>
-__device__ __forceinline__ void jmu_wave_form(const Args &a, double mu2, double *dst, int lane)
+__device__ __forceinline__ void jmu_wave_form(const Args &a, double mu2, double *dst)
 {
     if (a.poles)
-        jmu_wave_impl<false, true, GROUPED>(a, mu2, dst, lane);  // split needs single poles
+        jmu_block_impl<false, true, GROUPED, true, 64>(a, mu2, dst);  // split needs single poles
     else if (a.split)
-        jmu_wave_impl<true, false, GROUPED>(a, mu2, dst, lane);
+        jmu_block_impl<true, false, GROUPED, true, 64>(a, mu2, dst);
     else
-        jmu_wave_impl<false, false, GROUPED>(a, mu2, dst, lane);
+        jmu_block_impl<false, false, GROUPED, true, 64>(a, mu2, dst);
 }
 
 template <class Args>
-__device__ __forceinline__ void jmu_wave(const Args &a, double mu2, double *dst, int lane)
+__device__ __forceinline__ void jmu_wave(const Args &a, double mu2, double *dst)
 {
     if (a.n_grp > 0 && !a.num)
-        jmu_wave_form<true>(a, mu2, dst, lane);
+        jmu_wave_form<true>(a, mu2, dst);
     else
-        jmu_wave_form<false>(a, mu2, dst, lane);
+        jmu_wave_form<false>(a, mu2, dst);
 }
 
 __global__ void __launch_bounds__(64) jmu_kernel(ScanArgs a, double mu2, double *dst)
 {
-    jmu_wave(a, mu2, dst, threadIdx.x);
+    jmu_wave(a, mu2, dst);
+}
+
+// Folded node (s, 2w) of the angular rule, an odd rule's middle node last.
+__device__ __forceinline__ void folded_node(const ScanArgs &a, int j, double &s, double &w)
+{
+    const int np = a.n_a / 2;
+    s = j < np ? a.ang[3 * j] : 0.0;
+    w = j < np ? a.ang[3 * j + 1] : (j < np + a.n_a % 2 ? a.wmid : 0.0);
+}
+
+constexpr int kJmuThreads = 256;
+
+// For tables generated on the device (single poles, no numerator): block 0 the
+// subtraction coefficients, the others the group tables as group_table writes them
+// on the host (see there), one thread a group.
+template <bool SPLIT, bool GROUPED>
+__global__ void __launch_bounds__(kJmuThreads)
+jmu_groups_kernel(ScanArgs a, double mu2, double *dst, double *grp)
+{
+    if (blockIdx.x == 0) {
+        jmu_block_impl<SPLIT, false, GROUPED, false, kJmuThreads>(a, mu2, dst);
+        return;
+    }
+    const int b = (blockIdx.x - 1) * kJmuThreads + threadIdx.x;
+    const int tables = a.grp_mid ? 2 : 1, nodes = a.n_a / 2 + a.n_a % 2;
+    if (b >= tables * a.n_grp) return;
+    const double centre = b < a.n_grp ? 1.0 : 0.5;
+    double P[kGroupNodes + 1], N[kGroupNodes + 1];
+#pragma unroll
+    for (int i = 0; i <= kGroupNodes; ++i) P[i] = N[i] = 0.0;
+    P[0] = 1.0;
+#pragma unroll
+    for (int k = 0; k < kGroupNodes; ++k) {
+        const int j = b % a.n_grp + k * a.n_grp;
+        double s, w;
+        folded_node(a, j, s, w);
+        const double t = j < nodes ? s - centre : 0.0;
+#pragma unroll
+        for (int i = kGroupNodes; i >= 0; --i) {
+            if (i > k + 1) continue;
+            N[i] = fma(w, P[i], fma(-t, N[i], i > 0 ? N[i - 1] : 0.0));
+        }
+#pragma unroll
+        for (int i = kGroupNodes; i >= 0; --i) {
+            if (i > k + 1) continue;
+            P[i] = fma(-t, P[i], i > 0 ? P[i - 1] : 0.0);
+        }
+    }
+    double *o = grp + (size_t)kGroupDoubles * b;
+    const double W = N[kGroupNodes - 1];
+#pragma unroll
+    for (int i = 0; i < kGroupNodes; ++i) o[i] = P[i];
+#pragma unroll
+    for (int i = 0; i < kGroupNodes - 1; ++i) o[kGroupNodes + i] = N[i] / W;
+    o[kGroupDoubles - 1] = W;
 }
 
 // One wave per request: installs request i's argument record (staged[i]) in
 // its slot of the request table, and writes J_mu (and the Taylor
 // coefficients) of that request into the record's jmu slot.
-__global__ void __launch_bounds__(64) jmu_batch_kernel(ScanArgs *__restrict__ reqs,
-                                                       const ScanArgs *__restrict__ staged,
-                                                       const int *__restrict__ slots,
-                                                       const double *__restrict__ mu2, int n)
+__global__ void __launch_bounds__(64)
+jmu_batch_kernel(ScanArgs *__restrict__ reqs, const ScanArgs *__restrict__ staged,
+                 const int *__restrict__ slots, const double *__restrict__ mu2, int n)
 {
     static_assert(sizeof(ScanArgs) % sizeof(unsigned long long) == 0, "record size");
     const int i = blockIdx.x;
@@ -197,7 +265,7 @@ __global__ void __launch_bounds__(64) jmu_batch_kernel(ScanArgs *__restrict__ re
     auto *dst = reinterpret_cast<unsigned long long *>(reqs + slot);
     for (int k = threadIdx.x; k < words; k += 64) dst[k] = src[k];
     const auto &a = ro(staged)[i];
-    jmu_wave(a, mu2[i], const_cast<double *>(a.jmu), threadIdx.x);
+    jmu_wave(a, mu2[i], const_cast<double *>(a.jmu));
 }
 
 }  // namespace
@@ -241,6 +309,16 @@ hipError_t launch_scan(const ScanArgs &a, int precision, int lanes, hipStream_t 
 hipError_t launch_jmu(const ScanArgs &a, double mu2, double *dst, hipStream_t s)
 {
     hipLaunchKernelGGL(jmu_kernel, dim3(1), dim3(64), 0, s, a, mu2, dst);
+    return hipGetLastError();
+}
+
+hipError_t launch_jmu_groups(const ScanArgs &a, double mu2, double *dst, double *grp, hipStream_t s)
+{
+    const int groups = (a.grp_mid ? 2 : 1) * a.n_grp;
+    const auto kernel = a.split ? (a.n_grp > 0 ? jmu_groups_kernel<true, true> : jmu_groups_kernel<true, false>)
+                                : (a.n_grp > 0 ? jmu_groups_kernel<false, true> : jmu_groups_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(1 + (groups + kJmuThreads - 1) / kJmuThreads), dim3(kJmuThreads), 0, s,
+                       a, mu2, dst, grp);
     return hipGetLastError();
 }
 
