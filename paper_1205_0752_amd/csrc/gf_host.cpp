@@ -546,10 +546,9 @@ int auto_lanes(const ScanArgs &base, int precision, const gf_grid &g)
     return std::max(fill, std::min(want, work));
 }
 
-// Every tile is one 64-wide block of a one-dimensional launch (the y-plane
-// scan packs four to a 256-wide block), and a dispatch counts its work-items
-// in 32 bits: a launch holds at most (2^32 - 256) / 64 tiles.  At one lane
-// per point the largest grid (2^31 points) takes 2^25 tiles; more lanes per
+// Every tile is one 64-wide block of a one-dimensional launch, and a dispatch
+// counts its work-items in 32 bits: a launch holds at most (2^32 - 256) / 64
+// tiles.  At one lane per point the largest grid (2^31 points) takes 2^25 tiles; more lanes per
 // point on a grid that large are refused rather than launched.
 constexpr long long kMaxLaunchTiles = ((1LL << 32) - 256) / 64;
 
@@ -857,6 +856,8 @@ int gf_yscan_plan(const gf_plan_t *plan, double x_re, double x_im, const gf_grid
                     dev);
     gf::ScanArgs a = plan->base;
     if ((rc = gf::set_grid(a, *ygrid, 1)) != GF_OK) return rc;
+    // set_grid's bound on the pair sums' products is for a grid of x
+    a.unscaled = a.unscaled && std::max(std::hypot(x_re, x_im), plan->params.mu2) < std::ldexp(1.0, 26);
     a.out = static_cast<double *>(out);
     a.cls = nullptr;
     hipError_t e = gf::launch_yscan(a, x_re, x_im, plan->params.mu2, what,

@@ -75,3 +75,32 @@ def test_large_and_tiny_magnitudes_leave_the_groups():
     plan.close()
     go, co, cond = oracle.scan(p, q, grid, want_cond=True)
     check_fp64(g, go, cond)
+
+
+@pytest.mark.parametrize("x", [2.0 + 1.5j, -3.0, 1.5, 0.0, 1e-160 + 2e-160j, 4e9 - 1e9j, -1e120j])
+@pytest.mark.parametrize("what", [0, 1])
+@pytest.mark.parametrize("n_a,props", [(64, None), (63, None), (130, None),
+                                       (64, (((0.4, 1.0), (2.5, -0.3)), ((1.0, 0.6), (3.0, 0.4))))])
+def test_y_plane_groups_equal_the_pairs(x, what, n_a, props):
+    """The y-plane scan of an FP64 plan runs in groups, that of an FP32C plan over the
+    pairs, both in FP64: equal within the rounding of either, 64 eps of the
+    sums' condition (x = mu^2 leaves the difference exactly 0 on both)."""
+    from test_yplane import _cond
+    p = Params(1.0, 0.25, 1.5, 1e4)
+    grid = Grid(27, 21, -8.0, 8.0, -5.0, 5.0)
+    legs = Propagators(*props) if props else None
+    got = []
+    for prec in (gf.FP64, gf.FP32C):
+        plan = gf.Plan(p, Quadrature(16, n_a, 4, prec), legs)
+        got.append(gf.yscan_plan(plan, x, grid, what).cpu().numpy().ravel())
+        plan.close()
+    a, b = got
+    ys = oracle.grid_points(grid)
+    cond = np.zeros(ys.size)
+    for m, res in (props[0] if props else ((p.m1sq, 1.0),)):
+        cond += abs(res) * (_cond(x, ys, m, n_a) + (what and _cond(p.mu2, ys, m, n_a)))
+    if what:
+        second = props[1] if props else ((p.m2sq, 1.0),)
+        cond *= np.abs(ys) * sum(abs(res / (ys + m)) for m, res in second)
+    assert np.array_equal(np.isnan(a), np.isnan(b))
+    assert np.all(np.abs(a - b) <= 2 * 64 * EPS * cond)
