@@ -33,7 +33,7 @@ namespace {
 // PREC is the form of the angular sums (kPairs, kFp32c, kGroups).
 template <int PREC, int L, bool TAYLOR, bool SPLIT, bool POLES, class Args>
 __device__ __forceinline__ void process_tile(const Args &a, int tile, int lane, int row0,
-                                             int tiles_a)
+                                             int tiles_a, const float *lds = nullptr)
 {
     constexpr int P = 64 / L;
     constexpr int TW = P < 8 ? P : 8;
@@ -94,7 +94,7 @@ __device__ __forceinline__ void process_tile(const Args &a, int tile, int lane, 
                 double r, g;
                 radial_node<SPLIT>(a, pc, k, r, g);
                 const cd U = mk(fma(pc.dir.r, r, pc.x1.r), fma(pc.dir.i, r, pc.x1.i));
-                const cd A = angular_sum<PREC, SC>(a, U, mk(x4d.r * r, x4d.i * r));
+                const cd A = angular_sum<PREC, SC>(a, U, mk(x4d.r * r, x4d.i * r), lds);
                 const double br = r + cr;
                 const double gq = g * rcp64(fma(br, br, ci * ci));
                 const double wr = gq * br, wi = -(gq * ci);  // g / (r + c)
@@ -172,7 +172,7 @@ __device__ __forceinline__ void process_tile(const Args &a, int tile, int lane, 
                 radial_coeffs<SPLIT, POLES>(a, pc, k, U, V2, w);
                 cd N[3];
                 if (a.num) numerator_at(a, U, pc.x1, N);
-                cd A = angular_sum_p<PREC, POLES>(a, U, V2, ~0, a.num ? N : nullptr, ray_neg);
+                cd A = angular_sum_p<PREC, POLES>(a, U, V2, ~0, a.num ? N : nullptr, ray_neg, lds);
                 cd t = cmul(w, A);
                 sr += t.r;
                 si += t.i;
@@ -205,7 +205,7 @@ __device__ __forceinline__ void process_tile(const Args &a, int tile, int lane, 
             const bool num = POLES && a.num;
             if (num) numerator_at(a, U, pc.x1, N);
             A = PREC == kFp32c && res ? angular_sum_p<0, POLES>(a, U, V2, set, num ? N : nullptr)
-                                      : angular_sum_p<PREC, POLES>(a, U, V2, set, num ? N : nullptr);
+                                      : angular_sum_p<PREC, POLES>(a, U, V2, set, num ? N : nullptr, 0, lds);
         }
         cd t = cmul(w, A);
         sr += t.r;
@@ -266,11 +266,19 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a)
     // (written as one if-else: an early return gave the tail's pair loop
     // scalar-register spills)
     constexpr bool tail = L == 1 || (PREC == kFp32c && L == 2);
+    // not at many lanes per point, where a wave's few nodes do not repay the copy
+    // into LDS
+    const float *lds = nullptr;
+    if constexpr (PREC == kFp32c && L <= 8) {
+        __shared__ float squares[kLdsPairs];
+        load_squares(a, squares, threadIdx.x & 63);
+        lds = squares;
+    }
     if (tail && a.tail_tiles > 0 && wave >= a.n_tiles - a.tail_tiles)
         process_tile<PREC, kTailLanes, TAYLOR, SPLIT, POLES>(
-            a, wave - (a.n_tiles - a.tail_tiles), threadIdx.x & 63, a.tail_row0, a.tail_tiles_a);
+            a, wave - (a.n_tiles - a.tail_tiles), threadIdx.x & 63, a.tail_row0, a.tail_tiles_a, lds);
     else
-        process_tile<PREC, L, TAYLOR, SPLIT, POLES>(a, wave, threadIdx.x & 63, 0, a.tiles_a);
+        process_tile<PREC, L, TAYLOR, SPLIT, POLES>(a, wave, threadIdx.x & 63, 0, a.tiles_a, lds);
 }
 
 // Serving: a persistent launch over a packed list of (request, tile) items of
@@ -281,6 +289,12 @@ __device__ __forceinline__ void serve_loop(const ScanArgs *reqs, const WorkItem 
                                            unsigned *counter)
 {
     const int lane = threadIdx.x & 63;
+    const float *lds = nullptr;
+    float *squares = nullptr;
+    if constexpr (PREC == kFp32c) {
+        __shared__ float waves[4][kLdsPairs];  // a slice for each wave of the block
+        lds = squares = waves[threadIdx.x >> 6];
+    }
     for (;;) {
         unsigned w = 0;
         if (lane == 0) w = atomicAdd(counter, 1u);
@@ -289,7 +303,8 @@ __device__ __forceinline__ void serve_loop(const ScanArgs *reqs, const WorkItem 
         const int req = ro(items)[w].req;
         const int tile = ro(items)[w].tile;
         const auto &r = ro(reqs)[req];  // keeps the constant address space
-        process_tile<PREC, 1, true, SPLIT, POLES>(r, tile, lane, 0, r.tiles_a);
+        if constexpr (PREC == kFp32c) load_squares(r, squares, lane);
+        process_tile<PREC, 1, true, SPLIT, POLES>(r, tile, lane, 0, r.tiles_a, lds);
     }
 }
 
