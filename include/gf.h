@@ -375,8 +375,9 @@ int gf_cut_curve(const gf_params *params, double x_re, double x_im, int n, doubl
  * angles); where Im zeta changes sign between consecutive samples, the sign
  * change is located by 40 bisection steps on the contour parameter (t, or the
  * arc angle), and a crossing is counted when Re zeta at the midpoint of the
- * final interval lies in [0, 1].  Points with
- * bit 0 clear form the region where the real-axis contour is unharmed.  out:
+ * final interval lies in [0, 1].  (Only the samples whose sign of Im zeta is not
+ * known from its zeros on the part are computed; the map is the one that all
+ * of them give.)  Points with bit 0 clear form the region where the real-axis contour is unharmed.  out:
  * caller-owned device memory, n_re * n_im bytes [n_im][n_re]; asynchronous on
  * `stream`.  n_samples in [2, 2^20].  Errors: GF_EINVAL (also for the grid
  * checks of gf_scan_plan), GF_EDEVICE. */
@@ -387,7 +388,8 @@ int gf_obstruction_map(const gf_params *params, const gf_grid *grid, int n_sampl
  *
  * A server owns three HIP streams (one for staging and subtraction sums, two
  * that take the persistent launches in turn), a device-memory arena of
- * `device_budget_bytes` and a scheduler thread.  Submitted requests wait in
+ * `device_budget_bytes`, 4 MiB beside it for the angular tables' group
+ * coefficients, and a scheduler thread.  Submitted requests wait in
  * FIFO order until their output (16 bytes per point) and any node tables not
  * yet resident fit in the arena and a slot is free; admitted requests run
  * concurrently: each scheduler iteration packs wave tiles of every running
