@@ -596,6 +596,10 @@ int set_grid(ScanArgs &a, const gf_grid &g, int lanes)
 // split rule 5.07 -> 4.83; pole sums (a conjugate pair on the (p-k) leg, two
 // k-leg poles) at four lanes without a tail 9.33, at one lane with it 8.99,
 // and with a numerator 13.25 -> 12.57.
+// (All of these with the pair sums and scalar FP32 nodes.  With the grouped sums
+// and nodes from LDS, no tail -> tail: FP64 1024^2 3.48 -> 3.36, 2048^2 13.35 -> 13.23;
+// FP32C 1024^2 11.07 -> 10.74, 2048^2 42.05 -> 41.40; t^2 3.51 -> 3.39, split rule
+// 4.06 -> 3.92, pole sums 7.41 -> 7.10.)
 constexpr long long kTailMinRounds = 2;
 constexpr long long kTailPoints = 16;  // per resident wave, at one lane per point
 
