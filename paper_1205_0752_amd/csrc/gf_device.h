@@ -120,6 +120,16 @@ __device__ __forceinline__ void sincos_turn(double a, double *sn, double *cs)
     *cs = (k + 1) & 2 ? -w : w;
 }
 
+// The FP32C kernels (LIB) keep the library's.
+template <bool LIB>
+__device__ __forceinline__ void sincos_of(double a, double *sn, double *cs)
+{
+    if constexpr (LIB)
+        sincos(a, sn, cs);
+    else
+        sincos_turn(a, sn, cs);
+}
+
 __device__ __forceinline__ double angle_between(double a, double b)
 {
     double d = fabs(a - b);
@@ -158,7 +168,10 @@ constexpr int kInfoRValid = 1 << 24;
 // (about 1,090 VALU instructions a wave when the class rule, its mirror test
 // and the ray each took atan2, hypot and sincos anew): one 64^2 scan at 64 x 32
 // + 16 nodes, 64 lanes per point, 13.1 -> 10.8 us; 128^2 at 64 x 49 tanh-sinh
-// nodes 26.2 -> 24.0 us.
+// nodes 26.2 -> 24.0 us.  The FP32C kernels keep (cos phi, sin phi) (point_setup's
+// LIB): their sums round U^2 and V^2 to FP32 and choose a node's form by them, so
+// the last bit of a direction moves a result by up to FP32 rounding (5e-9 at one
+// point of a 352^2 scan, below FP32C's own error).
 struct PointArg {
     double r, v, phi;
 };
@@ -326,7 +339,7 @@ __device__ void split_boundaries(const Args &a, double xr, double xi, double *b)
     }
 }
 
-template <bool SPLIT = false, bool POLES = false, class Args>
+template <bool SPLIT = false, bool POLES = false, bool LIB = false, class Args>
 __device__ PointCtx point_setup(const Args &a, double xr, double xi, double r, double phi, int cls,
                                 int res_sign, int info = 0)
 {
@@ -341,13 +354,19 @@ __device__ PointCtx point_setup(const Args &a, double xr, double xi, double r, d
         for (int i = 0; i < 5; ++i) P.tb[i] = b[i];
     }
     if (cls == kY || cls == kYRes || cls == kLong) {
-        const double ir = rcp64c(r);
-        P.dir = mk(xr * ir, xi * ir);
+        if constexpr (LIB) {
+            double s, c;
+            sincos(phi, &s, &c);
+            P.dir = mk(c, s);
+        } else {
+            const double ir = rcp64c(r);
+            P.dir = mk(xr * ir, xi * ir);
+        }
         if (a.dim == 4) {
             P.dirD = cmul(P.dir, P.dir);
         } else if (a.dim == 3) {
             double s, c;
-            sincos_turn(0.5 * phi, &s, &c);
+            sincos_of<LIB>(0.5 * phi, &s, &c);
             P.dirD = cmul(P.dir, mk(c, s));
         } else {
             P.dirD = P.dir;
@@ -477,7 +496,7 @@ __device__ __forceinline__ void radial_coeffs(const Args &a, const PointCtx &P, 
 // arc runs from phi back to 0 through the half plane of x, the long arc
 // (kLong) from phi on to +-2 pi through the other one; the short rotation's
 // residues carry the sign of phi, the long rotation's the opposite sign.
-template <bool POLES, class Args>
+template <bool POLES, bool LIB = false, class Args>
 __device__ __forceinline__ bool outer_coeffs(const Args &a, const PointCtx &P, int k, cd &U,
                                              cd &V2, cd &w, int &set)
 {
@@ -504,7 +523,7 @@ __device__ __forceinline__ bool outer_coeffs(const Args &a, const PointCtx &P, i
             h = 0.5 * L * wa;
         }
         double s, c;
-        sincos_turn(psi, &s, &c);
+        sincos_of<LIB>(psi, &s, &c);
         const cd y = mk(a.lam2 * c, a.lam2 * s);
         U = cadd(P.x1, y);
         V2 = cmul(x4, y);
@@ -513,7 +532,7 @@ __device__ __forceinline__ bool outer_coeffs(const Args &a, const PointCtx &P, i
         if (a.dim == 3) {
             // the long arc's angle runs from phi -+ 2 pi back to 0 along the
             // contour: sqrt(y) = e^{i (psi -+ 2 pi)/2} Lambda = -e^{i psi/2} Lambda
-            sincos_turn(0.5 * psi, &s, &c);
+            sincos_of<LIB>(0.5 * psi, &s, &c);
             const double lam = lng ? -a.lam : a.lam;
             f = mk(lam * c, lam * s);
         } else if (a.dim == 2) {
@@ -550,7 +569,7 @@ __device__ __forceinline__ bool outer_coeffs(const Args &a, const PointCtx &P, i
         else if (P.phi > 0.0 && t > P.phi) t -= 2.0 * M_PI;
         else if (P.phi < 0.0 && t < P.phi) t += 2.0 * M_PI;
         double s, c;
-        sincos_turn(0.5 * t, &s, &c);
+        sincos_of<LIB>(0.5 * t, &s, &c);
         const double m = sqrt(hypot(y0.r, y0.i));
         return mk(m * c, m * s);
     };

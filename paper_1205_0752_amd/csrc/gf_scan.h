@@ -67,7 +67,7 @@ __device__ __forceinline__ void process_tile(const Args &a, int tile, int lane, 
             info = info_b;
         }
     }
-    const PointCtx pc = point_setup<SPLIT, POLES>(a, xr, xi, pa.r, phi, ecls, sign, info);
+    const PointCtx pc = point_setup<SPLIT, POLES, PREC == kFp32c>(a, xr, xi, pa.r, phi, ecls, sign, info);
 
     // The straight part's nodes, then the arc and residue nodes, in one
     // sequence k = s, s + L, ... per lane: two loops so that the arc's sine
@@ -185,7 +185,7 @@ __device__ __forceinline__ void process_tile(const Args &a, int tile, int lane, 
         // a residue node carries a whole 2 pi i Res with no quadrature weight
         // to shrink it, and its k-leg pole can sit near the angular cut: its
         // angular sum is taken in FP64 in every precision
-        const bool res = outer_coeffs<POLES>(a, pc, k, U, V2, w, set);
+        const bool res = outer_coeffs<POLES, PREC == kFp32c>(a, pc, k, U, V2, w, set);
         cd A;
         if constexpr (grouped) {
             // x - y = 2x - (x + y)
