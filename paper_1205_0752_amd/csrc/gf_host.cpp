@@ -245,8 +245,10 @@ size_t group_doubles(int na, int rule)
 // being (0, w_mid), so that each spreads over (0, 1):
 //   sum_j 2w_j / (sigma - s_j) = W N(v) / P(v),   v = sigma - centre,
 // P(v) = prod (v - t_j), t_j = s_j - centre, N the matching monic numerator and W
-// the sum of the weights.  Missing nodes are filled up with s = centre, weight
-// 0.  The first table's centre is s = 1, the second's 1/2.  Tanh-sinh has no
+// the sum of the weights.  Missing nodes are filled up with weight 0 at a place
+// where the table is never used, since their factor of N and P vanishes there:
+// s = 0 in the first table, whose centre is s = 1 (e = -1; at e = 0, the cut's end,
+// the sum is finite), and the centre in the second, whose centre is 1/2 (on the cut).  Tanh-sinh has no
 // second one: half of its nodes lie within 1e-2 of s = 1, where an expansion
 // about the middle would cancel (up to 1e5 eps next to that end; about s = 1 at
 // most 16).  The products run in long double, so the coefficients are rounded
@@ -263,7 +265,8 @@ void group_table(int na, int rule, const std::vector<double> &ang, double wmid,
         long double P[kGroupNodes + 1] = {1.0L}, N[kGroupNodes + 1] = {};
         for (int k = 0; k < kGroupNodes; ++k) {
             const int j = g + k * n_grp;
-            const long double s = j < np ? (long double)ang[3 * j] : (j < nodes ? 0.0L : centre);
+            const long double fill = b < n_grp ? 0.0L : centre;
+            const long double s = j < np ? (long double)ang[3 * j] : (j < nodes ? 0.0L : fill);
             const long double t = s - centre, w = j < np ? ang[3 * j + 1] : (j < nodes ? wmid : 0.0);
             // N <- N (v - t) + w P, then P <- P (v - t)
             for (int i = k + 1; i >= 0; --i) N[i] = (i > 0 ? N[i - 1] : 0.0L) - t * N[i] + w * P[i];

@@ -228,7 +228,8 @@ jmu_groups_kernel(ScanArgs a, double mu2, double *dst, double *grp)
         const int j = b % a.n_grp + k * a.n_grp;
         double s, w;
         folded_node(a, j, s, w);
-        const double t = j < nodes ? s - centre : 0.0;
+        // missing nodes: s = 0 in the first table, the centre in the second
+        const double t = j < nodes || b < a.n_grp ? s - centre : 0.0;
 #pragma unroll
         for (int i = kGroupNodes; i >= 0; --i) {
             if (i > k + 1) continue;

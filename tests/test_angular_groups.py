@@ -104,3 +104,46 @@ def test_y_plane_groups_equal_the_pairs(x, what, n_a, props):
         cond *= np.abs(ys) * sum(abs(res / (ys + m)) for m, res in second)
     assert np.array_equal(np.isnan(a), np.isnan(b))
     assert np.all(np.abs(a - b) <= 2 * 64 * EPS * cond)
+
+
+# full groups, one to seven missing nodes, an odd rule
+END_ORDERS = [96, 100, 111, 113, 128, 200]
+
+
+@pytest.mark.parametrize("n_a", END_ORDERS)
+def test_residue_at_the_end_of_the_cut(n_a):
+    """Masses -+ i/2 at their threshold x = -1: the residue node y = -m2^2 has
+    U^2 = V^2 exactly, e = 0, where only the filled-up nodes' factors could vanish."""
+    p, q = Params(-0.5j, 0.5j, 0.0, 1e6), Quadrature(64, n_a, 16)
+    grid = Grid(6, 3, -8.0, 4.0, -1.5, 1.5)
+    x = oracle.grid_points(grid)
+    assert -1.0 in x
+    go, co, cond = oracle.scan(p, q, grid, want_cond=True)
+    ok = co != oracle.SINGULAR
+    plan = gf.Plan(p, q)
+    for lanes in (1, 64):
+        g = gf.scan_plan(plan, grid, lanes=lanes).cpu().numpy().ravel()
+        check_fp64(g[ok], go[ok], cond[ok])
+    plan.close()
+    out = gf.empty_result(grid)
+    gf.scan_noalloc(p, grid, q, out)
+    check_fp64(out.cpu().numpy().ravel()[ok], go[ok], cond[ok])
+
+
+@pytest.mark.parametrize("n_a", END_ORDERS)
+def test_y_plane_at_the_end_of_the_cut(n_a):
+    """x = 2i, m1^2 = 1, y = 1 has U^2 = V^2 exactly; the angular average there is
+    U / V^2 sum_j 2w_j / (1 - s_j)."""
+    plan = gf.Plan(Params(1.0, 1.0, 1.0, 1e4), Quadrature(16, n_a, 4))
+    grid = Grid(3, 3, -2.0, 4.0, -1.5, 1.5)
+    y = oracle.grid_points(grid)
+    g = gf.yscan_plan(plan, 2j, grid, 0).cpu().numpy().ravel()
+    plan.close()
+    at = int(np.nonzero(y == 1.0)[0][0])
+    z, w = oracle.angular_rule(GC2, n_a)
+    keep = z > 1e-9 / n_a
+    want = (2 + 2j) / 8j * (np.sum(2.0 * w[keep] / (1.0 - z[keep] ** 2)) + np.sum(w[np.abs(z) <= 1e-9 / n_a]))
+    # 1 - z^2 rounds next to z = 1, the last node's by eps / (1 - z^2) ~ eps n^2 / 10 of a
+    # term that is a fraction ~ 1/n of the sum
+    assert abs(g[at] - want) <= (64 + n_a) * EPS * abs(want)
+    assert np.all(np.isfinite(g))
