@@ -105,11 +105,10 @@ __device__ __forceinline__ void process_tile(const Args &a, int tile, int lane, 
         if constexpr (grouped) {
             // e and h = U / V^2 of angular_sum_grouped with the mass terms put
             // into the point's constants, 1/r from the table
-            const StraightCtx st = straight_ctx(a, pc, pa.r, ecls == kR);
-            const cd m = mk(a.m1_re, a.m1_im);
+            const cd m = mk(a.m1_re, a.m1_im), x = mk(xr, xi);
+            const StraightCtx st = straight_ctx(a, pc, x, pa.r, ecls == kR);
             const cd h0 = cmul(pc.dir, st.kappa), h1 = cmul(pc.x1, st.kappa);
             const cd c0 = cadd(st.c0, cscale(cmul(m, h0), 2.0));
-            const cd x = mk(pc.x1.r - m.r, pc.x1.i - m.i);
             const cd b0 = cadd(st.b0, cmul(m, cmul(cadd(x, pc.x1), st.kappa)));
             for (; k < n_straight; k += L) {
                 double r, g, rinv;

@@ -147,3 +147,22 @@ def test_y_plane_at_the_end_of_the_cut(n_a):
     # term that is a fraction ~ 1/n of the sum
     assert abs(g[at] - want) <= (64 + n_a) * EPS * abs(want)
     assert np.all(np.isfinite(g))
+
+
+@pytest.mark.parametrize("lanes", [1, 16])
+@pytest.mark.parametrize("m1sq", [-1 + 1e-2j, -1 + 1e-3j, -1 + 1e-4j])
+def test_masses_next_to_the_negative_axis(m1sq, lanes):
+    """|x| far below |m1^2| on rays and the real axis: x must not carry the
+    rounding of x + m1^2, and U = x + y + m1^2 cancels along the contour."""
+    p, q = Params(m1sq, 1.0, 1.0, 1e4), Quadrature(256, 128, 16)
+    s = m1sq.imag ** 2
+    for h in (1e-2, 0.3, 1.0, 30.0):
+        grid = Grid(8, 6, -h * s, h * s, -h * s, h * s)
+        x = oracle.grid_points(grid)
+        _, co, cond = oracle.eval_points(p, q, x, want_cond=True)
+        go = oracle.eval_points_q_sets(p, q, x)
+        ok = co != oracle.SINGULAR
+        plan = gf.Plan(p, q)
+        g = gf.scan_plan(plan, grid, lanes=lanes).cpu().numpy().ravel()
+        plan.close()
+        check_fp64(g[ok], go[ok], cond[ok])
