@@ -1222,8 +1222,10 @@ __device__ __forceinline__ cd angular_sum_p(const Args &a, cd U, cd V2, int set 
 // iv = 1 / V^2 and a function for e0 = (x - y)^2 / V^2: with U = x + y + m^2,
 //   e = U^2 / V^2 - 1 = e0 + m^2 (2 (x + y) + m^2) iv.
 // The first form loses about 3 eps (1 + 1/|e|) of e, so the second (eps (1 +
-// |e|^-1/2) from the rounding of x - y) is taken for |e| < 1/2.  pairs(U) gives
-// the sum where no table applies.
+// |e|^-1/2) from the rounding of x - y) is taken for |e| < 1/2, unless its terms, of
+// order |m^2 / 4x| about |y| = |m^2|, cancel: |e0| >= 2 (a y plane at x = 1e-8, m = 1 next
+// to y = -1: 1.5e-8 of the sum lost there, 1e-10 by the first).  pairs(U) gives the sum
+// where no table applies.
 template <bool POLES, bool MIDDLE, class Args, class E0Fn, class PairsFn>
 __device__ __forceinline__ cd angular_sum_grouped_p(const Args &a, cd xy, cd iv, E0Fn e0,
                                                     PairsFn pairs, int set = ~0, int neg = 0)
@@ -1232,7 +1234,10 @@ __device__ __forceinline__ cd angular_sum_grouped_p(const Args &a, cd xy, cd iv,
         const cd U = cadd(xy, m), h = cmul(U, iv);
         cd e = cmul(U, h);
         e.r -= 1.0;
-        if (fma(e.r, e.r, e.i * e.i) < 0.25) e = cadd(e0(), cmul(iv, cmul(m, cadd(xy, U))));
+        if (fma(e.r, e.r, e.i * e.i) < 0.25) {
+            const cd t = e0();
+            if (fma(t.r, t.r, t.i * t.i) < 4.0) e = cadd(t, cmul(iv, cmul(m, cadd(xy, U))));
+        }
         return angular_sum_grouped<MIDDLE>(a, e, h, [&] { return pairs(U); });
     };
     if (!POLES) return one(mk(a.m1_re, a.m1_im));

@@ -166,3 +166,29 @@ def test_masses_next_to_the_negative_axis(m1sq, lanes):
         g = gf.scan_plan(plan, grid, lanes=lanes).cpu().numpy().ravel()
         plan.close()
         check_fp64(g[ok], go[ok], cond[ok])
+
+
+@pytest.mark.parametrize("ax", [1e-4, 1e-6, 1e-8, 1e-10])
+@pytest.mark.parametrize("n_a,rule", [(64, GC2), (129, TANH_SINH)])
+def test_y_plane_at_small_x(ax, n_a, rule):
+    """|x| far below m1^2, y next to -m1^2, where the terms of (x - y)^2 / V^2 and of the
+    masses cancel: the groups (an FP64 plan) stay within the rounding of U, S / |U| eps
+    with S = |x| + |y| + m1^2, times the sum's sensitivity (the cut's 1 / |D| included);
+    the pairs (an FP32C plan) carry the same."""
+    p = Params(1.0, 0.25, 1.5, 1e4)
+    x, h = ax * (1 + 0.3j), 3 * np.sqrt(ax)
+    grid = Grid(24, 24, -1 - h, -1 + h, -h, h)
+    y = oracle.grid_points(grid)
+    got = []
+    for prec in (gf.FP64, gf.FP32C):
+        plan = gf.Plan(p, Quadrature(16, n_a, 4, prec, rule))
+        got.append(gf.yscan_plan(plan, x, grid, 0).cpu().numpy().ravel())
+        plan.close()
+    z, w = oracle.angular_rule(rule, n_a)
+    U = x + y + 1.0
+    root = np.sqrt(4 * x * y)
+    d = U[:, None] - root[:, None] * z[None, :]
+    # |dA| <= sum |w / D^2| (|dU| + |dV z|), |dU| <= eps S, |dV| <= 2 eps |V|
+    S = np.abs(x) + np.abs(y) + 1.0
+    sens = np.sum(np.abs(w / d ** 2) * (S[:, None] + 2 * np.abs(root[:, None] * z)), axis=1)
+    assert np.all(np.abs(got[0] - got[1]) <= 64 * EPS * sens)
