@@ -17,8 +17,10 @@ __device__ __forceinline__ cd y_average(const ScanArgs &a, cd x, cd y)
             const cd d = mk(x.r - y.r, x.i - y.i);
             return cmul(cmul(d, d), iv);
         };
+        // the pairs always rescaled: a y grid may meet U = V = 0 (x = 0, y = -m1^2), where
+        // products of eight |D|^2 underflow however small the box
         return angular_sum_grouped_p<POLES, true>(a, xy, iv, e0, [&](cd U) {
-            return angular_sum64<-1, true>(a.ang, a.n_a / 2, a.wmid, U, V2, !a.unscaled);
+            return angular_sum64<1, true>(a.ang, a.n_a / 2, a.wmid, U, V2);
         });
     } else if constexpr (POLES) {
         return angular_sum_p<0, true>(a, cadd(xy, m1), V2);

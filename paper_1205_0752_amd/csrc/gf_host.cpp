@@ -863,8 +863,7 @@ int gf_yscan_plan(const gf_plan_t *plan, double x_re, double x_im, const gf_grid
                     dev);
     gf::ScanArgs a = plan->base;
     if ((rc = gf::set_grid(a, *ygrid, 1)) != GF_OK) return rc;
-    // set_grid's bound on the pair sums' products is for a grid of x
-    a.unscaled = a.unscaled && std::max(std::hypot(x_re, x_im), plan->params.mu2) < std::ldexp(1.0, 26);
+    a.unscaled = 0;  // set_grid's bound on the pair sums' products is for a grid of x
     a.out = static_cast<double *>(out);
     a.cls = nullptr;
     hipError_t e = gf::launch_yscan(a, x_re, x_im, plan->params.mu2, what,

@@ -192,3 +192,18 @@ def test_y_plane_at_small_x(ax, n_a, rule):
     S = np.abs(x) + np.abs(y) + 1.0
     sens = np.sum(np.abs(w / d ** 2) * (S[:, None] + 2 * np.abs(root[:, None] * z)), axis=1)
     assert np.all(np.abs(got[0] - got[1]) <= 64 * EPS * sens)
+
+
+@pytest.mark.parametrize("n_a", [64, 100, 129])
+def test_y_plane_at_the_pole_without_a_cut(n_a):
+    """x = 0: the cut has shrunk to y = -m1^2 and the sum is 1/U (sum w = n/(n+1) of it on
+    the Chebyshev rule) however close y comes; next to x = 0 it stays finite."""
+    plan = gf.Plan(Params(1.0, 0.25, 1.5, 1e4), Quadrature(16, n_a, 4))
+    for h in (1e-9, 1e-11, 1e-13):
+        grid = Grid(4, 4, -1 - h, -1 + h, -h, h)
+        y = oracle.grid_points(grid)
+        want = np.sum(oracle.angular_rule(GC2, n_a)[1]) / (y + 1.0)
+        g = gf.yscan_plan(plan, 0.0, grid, 0).cpu().numpy().ravel()
+        assert np.all(np.abs(g - want) <= 64 * EPS * np.abs(want))
+        assert np.all(np.isfinite(gf.yscan_plan(plan, 1e-30 + 1e-30j, grid, 0).cpu().numpy()))
+    plan.close()
