@@ -126,8 +126,14 @@ __device__ void cut_bisect(CutWalk &w, double lo, double hi, bool lo_pos)
 // samples a part: 3.5 ms when every sample was computed (7 to 10 VALU
 // instructions each, VALU-bound), 0.09 ms now; of that step 0.17 ms came from
 // the roots and the rest from settling most bisections by the roots (cut_settled).
+//
+// Up to kShortWalk samples a part, all of them are computed, which costs less than the
+// roots (1024^2 points, real masses: at 2 samples 27 us against 66, at 6 37 and 70, at 8
+// 65 and 72, at 12 100 and 76; complex masses 101 and 143, 117 and 147, 145 and 150,
+// 172 and 154).
 constexpr double kSampleTol = 1e-13;  // of the terms' magnitudes
 constexpr int kPad = 2;
+constexpr int kShortWalk = 8;
 
 // Root positions in units of samples, ascending (unused ones beyond any sample).
 struct Roots {
@@ -248,6 +254,27 @@ __device__ void cut_walk_straight(CutWalk &w, int n, double T)
         const double ui = REAL ? w.x1.i : fma(w.dir.i, e, w.x1.i);
         return fma(ur, fma(ui, c4r2, -(ur * c4.i)), ui * (ui * c4.i));
     };
+    Roots r = {{kNoRoot, kNoRoot, kNoRoot, kNoRoot}};
+    int at = -1;  // the recurrence's sample
+    double e = 0.0;
+    bool prev = false;
+    auto visit = [&](int k, bool fresh) {
+        if (w.hit) return;
+        const int anchor = ((k - 1) & ~63) + 1;
+        if (at < anchor || at >= k) {
+            at = anchor;
+            e = expm1(anchor * h);
+        }
+        for (; at < k; ++at) e = fma(e, c, e + c);
+        const bool p = value_at(e) > 0.0;
+        if (!fresh && p != prev && !cut_settled(w, r, h, k))
+            cut_bisect(w, fma((double)(k - 1), h, 0.0), fma((double)k, h, 0.0), prev);
+        prev = p;
+    };
+    if (n <= kShortWalk) {
+        for (int k = 1; k < n; ++k) visit(k, k == 1);
+        return;
+    }
     // f = q2 e^2 + q1 e + q0
     const cd cc = mk(c4.r, -c4.i), d2 = cmul(w.dir, w.dir), xd = cmul(w.x1, w.dir),
              x2 = cmul(w.x1, w.x1);
@@ -261,7 +288,6 @@ __device__ void cut_walk_straight(CutWalk &w, int n, double T)
     const double b2 = fma(tr, dr * di, ti * fma(dr, dr, di * di));
     const double b1 = fma(tr, fma(xr, di, xi * dr), 2.0 * ti * fma(xr, dr, xi * di));
     const double b0 = fma(tr, xr * xi, ti * fma(xr, xr, xi * xi));
-    Roots r;
     const double ih = 1.0 / h, top = w.lam2 * 1.01;
     auto place = [&](double e) { return e > 0.0 && e < top ? log1p(e) * ih : kNoRoot; };
     // two roots next to one another share the logarithm
@@ -280,22 +306,7 @@ __device__ void cut_walk_straight(CutWalk &w, int n, double T)
         const double e = expm1(t * h);
         return fabs(fma(fma(q2, e, q1), e, q0)) <= fma(fma(b2, e, b1), e, b0);
     };
-    int at = -1;  // the recurrence's sample
-    double e = 0.0;
-    bool prev = false;
-    visit_undecided(r, 1, n, false, inside, [&](int k, bool fresh) {
-        if (w.hit) return;
-        const int anchor = ((k - 1) & ~63) + 1;
-        if (at < anchor || at >= k) {
-            at = anchor;
-            e = expm1(anchor * h);
-        }
-        for (; at < k; ++at) e = fma(e, c, e + c);
-        const bool p = value_at(e) > 0.0;
-        if (!fresh && p != prev && !cut_settled(w, r, h, k))
-            cut_bisect(w, fma((double)(k - 1), h, 0.0), fma((double)k, h, 0.0), prev);
-        prev = p;
-    });
+    visit_undecided(r, 1, n, false, inside, visit);
 }
 
 // Samples along an arc from angle phi, psi_k = phi + span k/(n-1), k = 0..n-1
@@ -321,6 +332,28 @@ __device__ void cut_walk_arc(CutWalk &w, int n, double phi, double span)
     const cd B = cscale(cx4, l4);
     const double alpha = 2.0 * l2 * fma(cx4.r, w.x1.i, cx4.i * w.x1.r);
     const double bc = A.i + B.i, bs = B.r - A.r;
+    int at = -1;
+    cd e = mk(1.0, 0.0);
+    bool prev = false;
+    auto visit = [&](int k, bool fresh) {
+        if (w.hit) return;
+        const int anchor = k & ~63;
+        if (at < anchor || at >= k) {
+            at = anchor;
+            double sn, cs;
+            sincos(fma((double)anchor, dpsi, phi), &sn, &cs);
+            e = mk(cs, sn);
+        }
+        for (; at < k; ++at) e = cmul(e, rot);
+        const bool p = fma(bc, e.r, fma(bs, e.i, alpha)) > 0.0;
+        if (!fresh && p != prev)
+            cut_bisect(w, fma((double)(k - 1), dpsi, phi), fma((double)k, dpsi, phi), prev);
+        prev = p;
+    };
+    if (n <= kShortWalk) {
+        for (int k = 0; k < n; ++k) visit(k, k == 0);
+        return;
+    }
     if (alpha == 0.0 && bc == 0.0 && bs == 0.0) return;
     const double bound = kSampleTol * (fabs(alpha) + fabs(bc) + fabs(bs));
     // f = alpha + R cos(psi - psi0) = +-bound; on an arc of nearly a whole turn
@@ -346,24 +379,6 @@ __device__ void cut_walk_arc(CutWalk &w, int n, double phi, double span)
         double sn, cs;
         sincos(fma(t, dpsi, phi), &sn, &cs);
         return fabs(fma(bc, cs, fma(bs, sn, alpha))) <= bound;
-    };
-    int at = -1;
-    cd e = mk(1.0, 0.0);
-    bool prev = false;
-    auto visit = [&](int k, bool fresh) {
-        if (w.hit) return;
-        const int anchor = k & ~63;
-        if (at < anchor || at >= k) {
-            at = anchor;
-            double sn, cs;
-            sincos(fma((double)anchor, dpsi, phi), &sn, &cs);
-            e = mk(cs, sn);
-        }
-        for (; at < k; ++at) e = cmul(e, rot);
-        const bool p = fma(bc, e.r, fma(bs, e.i, alpha)) > 0.0;
-        if (!fresh && p != prev)
-            cut_bisect(w, fma((double)(k - 1), dpsi, phi), fma((double)k, dpsi, phi), prev);
-        prev = p;
     };
     visit_undecided(r, 0, n, ends, inside, visit);
 }

@@ -30,3 +30,10 @@ def test_map_equals_the_full_walk(p, n):
         want, tie = oracle.obstruction(p, oracle.grid_points(grid), n)
         bad = (got != want) & ~tie
         assert not np.any(bad), (grid, np.nonzero(bad)[0][:5])
+
+
+@pytest.mark.parametrize("n", [2, 3, 7, 8, 9, 16])
+@pytest.mark.parametrize("p", MASSES, ids=["real", "conjugate", "complex", "unequal"])
+def test_short_walks_compute_every_sample(p, n):
+    """Up to eight samples a part are all computed, more go by the roots."""
+    test_map_equals_the_full_walk(p, n)
