@@ -17,14 +17,15 @@ namespace {
 //   2w U N0 + 2w z^2 (V^2/2) N1 + 2w z^2 (V^2 U/4) N2,   V^2 = 4 (mu^2 + delta) y,
 // a quadratic A = a0 + a1 delta + a2 delta^2 in delta.  The middle node
 // (z = 0) w_mid N0 / (U0 + delta) has q_i = w_mid N0 (-1)^i / U0^(i+1).
-// acc[i] += omega q_i for i = 1..n.
+// acc[i] += omega q_i for i = 1..n, over the pairs j0, j0 + step, .. (the middle node
+// with j0 = 0).
 template <class Args>
 __device__ void taylor_node(const Args &a, cd U0, double y, cd omega, int n, cd *acc,
-                            const cd *N = nullptr)
+                            const cd *N = nullptr, int j0 = 0, int step = 1)
 {
     const double *tab = a.ang;
     const double mu2 = a.mu2;
-    for (int j = 0; j < a.n_a / 2; ++j) {
+    for (int j = j0; j < a.n_a / 2; j += step) {
         const double z2 = ro(tab)[3 * j], w2 = ro(tab)[3 * j + 1];
         const cd D0 = mk(U0.r * U0.r - U0.i * U0.i - 4.0 * mu2 * y * z2, 2.0 * U0.r * U0.i);
         const cd D1 = mk(2.0 * U0.r - 4.0 * y * z2, 2.0 * U0.i);
@@ -53,7 +54,7 @@ __device__ void taylor_node(const Args &a, cd U0, double y, cd omega, int n, cd 
             qm1 = q;
         }
     }
-    if (a.wmid != 0.0) {
+    if (j0 == 0 && a.wmid != 0.0) {
         const cd rU = cdiv(mk(1.0, 0.0), U0);
         cd p = cscale(rU, a.wmid);
         if (N) p = cmul(p, N[0]);
@@ -65,18 +66,18 @@ __device__ void taylor_node(const Args &a, cd U0, double y, cd omega, int n, cd 
 }
 
 // <1/(U - V z)> pair by pair from the direct denominators, each reciprocal with a
-// cubic step.
+// cubic step; over the pairs j0, j0 + step, .. (the middle node with j0 = 0).
 template <class Args>
-__device__ cd pairs_one_by_one(const Args &a, cd U, cd V2)
+__device__ cd pairs_one_by_one(const Args &a, cd U, cd V2, int j0 = 0, int step = 1)
 {
     const auto *t = ro(a.ang);
     const cd U2 = cmul(U, U);
     cd A = mk(0.0, 0.0);
-    for (int j = 0; j < a.n_a / 2; ++j)
+    for (int j = j0; j < a.n_a / 2; j += step)
         A = cadd(A, cscale(cinv(mk(fma(-V2.r, t[3 * j], U2.r), fma(-V2.i, t[3 * j], U2.i))),
                            t[3 * j + 1]));
     A = cmul(A, U);
-    if (a.wmid != 0.0) A = cadd(A, cscale(cinv(U), a.wmid));
+    if (j0 == 0 && a.wmid != 0.0) A = cadd(A, cscale(cinv(U), a.wmid));
     return A;
 }
 
@@ -95,7 +96,11 @@ __device__ cd pairs_one_by_one(const Args &a, cd U, cd V2)
 // THREADS = 64: one wave per request finds room between the blocks of scans that are
 // running (blocks of four waves waited 5 ms for it, 0.2 ms by one wave, behind
 // two serve kernels), and a plan computes J once.  THREADS = 256 where it is
-// computed on every call: a node per thread.
+// computed on every call; without TABLES up to 256 nodes each of the four waves takes
+// every fourth pair of all nodes, a node a lane, and beyond that a thread takes whole
+// nodes (the allocation-free call, 16^2 points, whole nodes and dealt pairs: 64 x 3000
+// nodes 305 and 193 us, 64 x 96 25.3 and 20.8, 256 x 96 33.0 and 31.4, 1024 x 128 82.6 and 84.6,
+// 2000 x 64 111 and 120).
 template <bool SPLIT, bool POLES, bool GROUPED, bool TABLES, int THREADS, class Args>
 __device__ __forceinline__ void jmu_block_impl(const Args &a, double mu2, double *dst)
 {
@@ -106,7 +111,9 @@ __device__ __forceinline__ void jmu_block_impl(const Args &a, double mu2, double
     double sr = 0.0, si = 0.0;
     cd acc[GF_MAX_TAYLOR + 1];
     for (int i = 0; i <= GF_MAX_TAYLOR; ++i) acc[i] = mk(0.0, 0.0);
-    for (int k = tid; k < pc.nodes; k += THREADS) {
+    const bool by_wave = GROUPED && !TABLES && pc.nodes <= THREADS;  // pairs dealt to the waves
+    const int j0 = by_wave ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0, step = by_wave ? kWaves : 1;
+    for (int k = by_wave ? tid & 63 : tid; k < pc.nodes; k += by_wave ? 64 : THREADS) {
         cd U, V2, w;
         node_coeffs<SPLIT, POLES>(a, pc, k, U, V2, w);
         cd N[3];
@@ -123,7 +130,7 @@ __device__ __forceinline__ void jmu_block_impl(const Args &a, double mu2, double
                     a, mk(mu2 + r, 0.0), iv, e0, [&](cd Ua) { return pairs_one_by_one(a, Ua, V2); });
             } else {
                 static_assert(TABLES || !POLES, "scans on device tables have single poles");
-                A = pairs_one_by_one(a, U, V2);
+                A = pairs_one_by_one(a, U, V2, j0, step);
             }
             if (!POLES) w = cscale(cinv(mk(r + a.m2_re, a.m2_im)), g);
         } else {
@@ -136,7 +143,7 @@ __device__ __forceinline__ void jmu_block_impl(const Args &a, double mu2, double
             double r, g;
             radial_node<SPLIT>(a, pc, k, r, g);
             if (!POLES) {
-                taylor_node(a, U, r, w, a.n_taylor, acc);
+                taylor_node(a, U, r, w, a.n_taylor, acc, nullptr, j0, step);
             } else {
                 for (int p = 0; p < a.n1; ++p) {  // pole a of P1: U_a, weight c1_a omega
                     const auto *q = &a.p1[4 * p];
