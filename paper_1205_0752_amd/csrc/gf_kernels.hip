@@ -213,7 +213,10 @@ constexpr int kJmuThreads = 256;
 
 // For tables generated on the device (single poles, no numerator): block 0 the
 // subtraction coefficients, the others the group tables as group_table writes them
-// on the host (see there), one thread a group.
+// on the host (see there), one thread a group.  The products run in pairs of doubles, so
+// that the coefficients are rounded once as there (in single doubles they are up to 210
+// eps off for 512 nodes, and a sum about the middle up to 77 eps for 127, 31 in pairs); they
+// take no time, the block beside them being longer (64 x 8192 nodes 499 us either way).
 template <bool SPLIT, bool GROUPED>
 __global__ void __launch_bounds__(kJmuThreads)
 jmu_groups_kernel(ScanArgs a, double mu2, double *dst, double *grp)
@@ -226,35 +229,57 @@ jmu_groups_kernel(ScanArgs a, double mu2, double *dst, double *grp)
     const int tables = a.grp_mid ? 2 : 1, nodes = a.n_a / 2 + a.n_a % 2;
     if (b >= tables * a.n_grp) return;
     const double centre = b < a.n_grp ? 1.0 : 0.5;
-    double P[kGroupNodes + 1], N[kGroupNodes + 1];
+    // coefficients as pairs of doubles
+    struct two {
+        double h, l;
+    };
+    // c + x y
+    auto add_mul = [](two c, two x, two y) {
+        const double p = x.h * y.h;
+        const double pl = fma(x.h, y.l, fma(x.l, y.h, fma(x.h, y.h, -p)));
+        const double t = c.h + p, z = t - c.h;
+        const double tl = (c.h - (t - z)) + (p - z);
+        return two{t, c.l + (tl + pl)};
+    };
+    two P[kGroupNodes + 1], N[kGroupNodes + 1];
 #pragma unroll
-    for (int i = 0; i <= kGroupNodes; ++i) P[i] = N[i] = 0.0;
-    P[0] = 1.0;
+    for (int i = 0; i <= kGroupNodes; ++i) P[i] = N[i] = two{0.0, 0.0};
+    P[0].h = 1.0;
 #pragma unroll
     for (int k = 0; k < kGroupNodes; ++k) {
         const int j = b % a.n_grp + k * a.n_grp;
         double s, w;
         folded_node(a, j, s, w);
         // missing nodes: s = 0 in the first table, the centre in the second
-        const double t = j < nodes || b < a.n_grp ? s - centre : 0.0;
-#pragma unroll
-        for (int i = kGroupNodes; i >= 0; --i) {
-            if (i > k + 1) continue;
-            N[i] = fma(w, P[i], fma(-t, N[i], i > 0 ? N[i - 1] : 0.0));
+        two t{0.0, 0.0};  // centre - s
+        if (j < nodes || b < a.n_grp) {
+            t.h = centre - s;
+            const double z = t.h - centre;
+            t.l = (centre - (t.h - z)) - (s + z);
         }
 #pragma unroll
         for (int i = kGroupNodes; i >= 0; --i) {
             if (i > k + 1) continue;
-            P[i] = fma(-t, P[i], i > 0 ? P[i - 1] : 0.0);
+            N[i] = add_mul(add_mul(i > 0 ? N[i - 1] : two{0.0, 0.0}, t, N[i]), two{w, 0.0}, P[i]);
+        }
+#pragma unroll
+        for (int i = kGroupNodes; i >= 0; --i) {
+            if (i > k + 1) continue;
+            P[i] = add_mul(i > 0 ? P[i - 1] : two{0.0, 0.0}, t, P[i]);
         }
     }
     double *o = grp + (size_t)kGroupDoubles * b;
-    const double W = N[kGroupNodes - 1];
+    const two W = N[kGroupNodes - 1];
+    const double Wh = W.h + W.l, iW = 1.0 / Wh;
+    const double Wl = W.h - Wh + W.l;  // |W.h| >= |W.l|
 #pragma unroll
-    for (int i = 0; i < kGroupNodes; ++i) o[i] = P[i];
+    for (int i = 0; i < kGroupNodes; ++i) o[i] = P[i].h + P[i].l;
 #pragma unroll
-    for (int i = 0; i < kGroupNodes - 1; ++i) o[kGroupNodes + i] = N[i] / W;
-    o[kGroupDoubles - 1] = W;
+    for (int i = 0; i < kGroupNodes - 1; ++i) {
+        const double q = (N[i].h + N[i].l) * iW;  // one step from the quotient in the pair
+        o[kGroupNodes + i] = fma(fma(-q, Wh, N[i].h) + fma(-q, Wl, N[i].l), iW, q);
+    }
+    o[kGroupDoubles - 1] = Wh;
 }
 
 // One wave per request: installs request i's argument record (staged[i]) in
