@@ -1024,7 +1024,7 @@ __device__ __forceinline__ void angular_sums64_num(const double *table, int npai
 // 512 x 256 nodes 11.42 -> 10.70 ms (10.98 with four), same bits; loading the next
 // step ahead 11.07.
 constexpr int kBlock = 16;
-constexpr int kLdsPairs = 512;  // 2 KiB a wave: 24 waves of a CU take 48 of its 160 KiB
+// The table takes 2 KiB a wave (kLdsPairs): 20 waves of a CU take 40 of its 160 KiB.
 
 // z_j^2 of the FP32 table into the wave's LDS.  Only this wave reads it, so the
 // wave's own order of LDS operations is enough.

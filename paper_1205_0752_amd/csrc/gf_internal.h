@@ -118,14 +118,18 @@ hipError_t launch_jmu_batch(ScanArgs *reqs, const ScanArgs *staged, const int *s
 
 // Form of the angular sums a kernel runs: FP64 over pairs, FP32C, FP64 over the
 // rule's groups.
-enum : int { kPairs = 0, kFp32c = 1, kGroups = 2 };
+enum : int { kPairs = 0, kFp32c = 1, kGroups = 2, kFp32cSix = 3 };
 int scan_form(const ScanArgs &a, int precision);
+// the form that serves it: plain FP32C requests beyond the LDS table run the six-wave kernel
+int serve_form(const ScanArgs &a, int precision);
 
 using ScanKernel = void (*)(ScanArgs);
 using ServeKernel = void (*)(const ScanArgs *, const WorkItem *, int, unsigned *);
 ScanKernel scan_kernel_groups(int lanes, bool taylor, bool split, bool poles);
 ScanKernel scan_kernel_pairs(int lanes, bool taylor, bool split, bool poles);
 ScanKernel scan_kernel_fp32c(int lanes, bool taylor, bool split, bool poles);
+ScanKernel scan_kernel_fp32c_six(int lanes, bool taylor);  // plain scans
+ServeKernel serve_kernel_fp32c_six();
 ServeKernel serve_kernel_groups(bool split, bool poles);
 ServeKernel serve_kernel_pairs(bool split, bool poles);
 ServeKernel serve_kernel_fp32c(bool split, bool poles);
@@ -189,6 +193,9 @@ size_t align256(size_t b);
 // n0..n6 below its leading 1, and the numerator's scale.
 constexpr int kGroupNodes = 8;
 constexpr int kGroupDoubles = 2 * kGroupNodes;
+
+// FP32C node pairs that a wave's LDS table holds.
+constexpr int kLdsPairs = 512;
 
 // Lanes per point of the tail of a one-lane scan.
 constexpr int kTailLanes = 16;

@@ -309,6 +309,12 @@ int scan_form(const ScanArgs &a, int precision)
     return a.n_grp > 0 && !a.num ? kGroups : kPairs;
 }
 
+int serve_form(const ScanArgs &a, int precision)
+{
+    const int form = scan_form(a, precision);
+    return form == kFp32c && !a.poles && !a.split && a.n_a / 2 > kLdsPairs ? kFp32cSix : form;
+}
+
 namespace {
 
 ScanKernel scan_kernel(int form, int lanes, bool taylor, bool split, bool poles)
@@ -324,7 +330,20 @@ ServeKernel serve_kernel(int form, bool split, bool poles)
     return form == kGroups  ? serve_kernel_groups(split, poles)
            : form == kPairs ? serve_kernel_pairs(split, poles)
            : form == kFp32c ? serve_kernel_fp32c(split, poles)
-                            : nullptr;
+           : form == kFp32cSix ? serve_kernel_fp32c_six()
+                               : nullptr;
+}
+
+// FP32C plain scans without the LDS table (more pairs than it holds, or many lanes per
+// point) whose waves are mostly inner loop run best at six waves per SIMD (see
+// scan_kernel_fp32c_six): from 2048 pairs a lane on, where more tiles than one round of
+// the other kernel's waves are there to fill them.
+bool fp32c_six(const ScanArgs &a, int lanes)
+{
+    if (a.poles || a.split) return false;
+    const long long np = a.n_a / 2, nodes = ((long long)a.n_r + a.n_arc + lanes) / lanes;
+    return (lanes >= 16 || np > kLdsPairs) && np * nodes >= 2048 &&
+           a.n_tiles > scan_resident_waves(kFp32c, lanes, a.n_taylor > 0, false, false);
 }
 
 }  // namespace
@@ -332,8 +351,10 @@ ServeKernel serve_kernel(int form, bool split, bool poles)
 hipError_t launch_scan(const ScanArgs &a, int precision, int lanes, hipStream_t s)
 {
     if (a.n_tiles <= 0) return hipSuccess;
-    const ScanKernel k =
-        scan_kernel(scan_form(a, precision), lanes, a.n_taylor > 0, a.split != 0, a.poles != 0);
+    const int form = scan_form(a, precision);
+    const ScanKernel k = form == kFp32c && fp32c_six(a, lanes)
+                             ? scan_kernel_fp32c_six(lanes, a.n_taylor > 0)
+                             : scan_kernel(form, lanes, a.n_taylor > 0, a.split != 0, a.poles != 0);
     if (!k) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k, dim3(a.n_tiles), dim3(64), 0, s, a);
     return hipGetLastError();

@@ -257,7 +257,10 @@ __device__ __forceinline__ void process_tile(const Args &a, int tile, int lane, 
 // it drains (waves sharing a SIMD progress oldest first, so a SIMD's last
 // waves end one by one), where otherwise SIMDs would run one or two waves that
 // cannot hide the reciprocal's latency.
-template <int PREC, int L, bool TAYLOR, bool SPLIT, bool POLES>
+//
+// LDS (FP32C): the nodes from LDS, not at many lanes per point, where a wave's few
+// nodes do not repay the copy.
+template <int PREC, int L, bool TAYLOR, bool SPLIT, bool POLES, bool LDS = false>
 __device__ __forceinline__ void scan_body(const ScanArgs &a)
 {
     const int wave = blockIdx.x;
@@ -265,10 +268,8 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a)
     // (written as one if-else: an early return gave the tail's pair loop
     // scalar-register spills)
     constexpr bool tail = L == 1 || (PREC == kFp32c && L == 2);
-    // not at many lanes per point, where a wave's few nodes do not repay the copy
-    // into LDS
     const float *lds = nullptr;
-    if constexpr (PREC == kFp32c && L <= 8) {
+    if constexpr (LDS) {
         __shared__ float squares[kLdsPairs];
         load_squares(a, squares, threadIdx.x & 63);
         lds = squares;
@@ -283,14 +284,14 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a)
 // Serving: a persistent launch over a packed list of (request, tile) items of
 // many requests.  Each wave takes the next item from a device counter (one
 // lane's atomic, broadcast) until the list is exhausted, so every wave exits.
-template <int PREC, bool SPLIT, bool POLES>
+template <int PREC, bool SPLIT, bool POLES, bool LDS = false>
 __device__ __forceinline__ void serve_loop(const ScanArgs *reqs, const WorkItem *items, int n_items,
                                            unsigned *counter)
 {
     const int lane = threadIdx.x & 63;
     const float *lds = nullptr;
     float *squares = nullptr;
-    if constexpr (PREC == kFp32c) {
+    if constexpr (LDS) {
         __shared__ float waves[4][kLdsPairs];  // a slice for each wave of the block
         lds = squares = waves[threadIdx.x >> 6];
     }
@@ -302,7 +303,7 @@ __device__ __forceinline__ void serve_loop(const ScanArgs *reqs, const WorkItem 
         const int req = ro(items)[w].req;
         const int tile = ro(items)[w].tile;
         const auto &r = ro(reqs)[req];  // keeps the constant address space
-        if constexpr (PREC == kFp32c) load_squares(r, squares, lane);
+        if constexpr (LDS) load_squares(r, squares, lane);
         process_tile<PREC, 1, true, SPLIT, POLES>(r, tile, lane, 0, r.tiles_a, lds);
     }
 }

@@ -120,7 +120,7 @@ struct Request {
     size_t out_off = 0, out_bytes = 0;
     std::string keys[3];  // radial, angular, arc table keys
     int lanes = 1;
-    int form = 0;  // of the angular sums (gf::scan_form)
+    int form = 0;  // of the angular sums (gf::serve_form)
     long long n_tiles = 0, next_tile = 0, tiles_done = 0;
     double cost_per_tile = 0.0;
     Clock::time_point t_submit, t_done;
@@ -160,7 +160,7 @@ struct Batch {
 constexpr int kMaxInflight = 3;
 constexpr int kStages = kMaxInflight + 1;  // one per batch in flight + the one being filled
 constexpr int kComputeStreams = 2;
-constexpr int kMaxGroups = 9;  // form x (plain, split, pole sums)
+constexpr int kMaxGroups = 10;  // form x (plain, split, pole sums), plain six-wave FP32C
 constexpr size_t kStageBytes = 32u << 20;
 constexpr long long kMaxItemsPerBatch = 1 << 20;
 // The angular tables' group coefficients live beside the budgeted arena (like
@@ -405,7 +405,7 @@ bool gf_server::admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
     a.out = reinterpret_cast<double *>(d_arena + out_off);
     a.cls = nullptr;
     r->n_tiles = a.n_tiles;
-    r->form = gf::scan_form(a, r->q.precision);
+    r->form = gf::serve_form(a, r->q.precision);
     r->state = GF_REQ_RUNNING;
     fresh.push_back(r);
     return true;
