@@ -388,8 +388,9 @@ int gf_obstruction_map(const gf_params *params, const gf_grid *grid, int n_sampl
  *
  * A server owns three HIP streams (one for staging and subtraction sums, two
  * that take the persistent launches in turn), a device-memory arena of
- * `device_budget_bytes`, 4 MiB beside it for the angular tables' group
- * coefficients, and a scheduler thread.  Submitted requests wait in
+ * `device_budget_bytes`, buffers of 4 MiB beside it for the group coefficients
+ * of the angular rules that FP64 requests in it use (one holds 31 of the largest
+ * rules), and a scheduler thread.  Submitted requests wait in
  * FIFO order until their output (16 bytes per point) and any node tables not
  * yet resident fit in the arena and a slot is free; admitted requests run
  * concurrently: each scheduler iteration packs wave tiles of every running

@@ -94,18 +94,23 @@ private:
     size_t size_ = 0, used_ = 0, peak_ = 0;
 };
 
-// A node table resident in the arena, shared by requests with the same key.
+// A node table (or a rule's group coefficients) resident in an arena, shared by
+// requests with the same key.
 struct Table {
+    Arena *from = nullptr;
+    char *dev = nullptr;     // device address
     size_t off = 0, bytes = 0;
     int refs = 0;
     std::vector<char> host;  // contents, uploaded through a staging buffer
     bool uploaded = false;
     double wmid = 0.0;       // angular tables: middle-node weight
     size_t off32 = 0;        // angular tables: offset of the FP32 pair table
-    // angular tables: the groups' coefficients, a range of the group arena (empty
-    // for a rule whose sums run pair by pair)
-    size_t grp_off = 0;
-    std::vector<char> grp_host;
+};
+
+// A buffer for group coefficients.
+struct GroupBuffer {
+    char *d = nullptr;
+    Arena arena;
 };
 
 struct Request {
@@ -118,7 +123,8 @@ struct Request {
     int state = GF_REQ_QUEUED;
     int slot = -1;
     size_t out_off = 0, out_bytes = 0;
-    std::string keys[3];  // radial, angular, arc table keys
+    int n_keys = 3;
+    std::string keys[4];  // radial, angular, arc table keys, the groups' where it has them
     int lanes = 1;
     int form = 0;  // of the angular sums (gf::serve_form)
     long long n_tiles = 0, next_tile = 0, tiles_done = 0;
@@ -163,10 +169,11 @@ constexpr int kComputeStreams = 2;
 constexpr int kMaxGroups = 10;  // form x (plain, split, pole sums), plain six-wave FP32C
 constexpr size_t kStageBytes = 32u << 20;
 constexpr long long kMaxItemsPerBatch = 1 << 20;
-// The angular tables' group coefficients live beside the budgeted arena (like
-// the staging buffers), so that the budget admits what it admitted by outputs
-// and node tables alone: 32 bytes per folded node, 128 KiB for the largest rule.
-constexpr size_t kGroupArenaBytes = 4u << 20;
+// The angular rules' group coefficients live beside the budgeted arena (like the
+// staging buffers), so that the budget admits requests by outputs and node tables
+// alone: 32 bytes per folded node, 128 KiB for the largest rule, only for rules
+// that an FP64 request in the server uses.  When those fill a buffer another is taken.
+constexpr size_t kGroupBufferBytes = 4u << 20;
 constexpr int kMaxNewPerBatch = 256;
 
 }  // namespace
@@ -184,8 +191,7 @@ struct gf_server {
     long long fill_min = 0, fill_max = 0;
     char *d_arena = nullptr;
     Arena arena;
-    char *d_groups = nullptr;
-    Arena groups_arena;
+    std::deque<GroupBuffer> groups;  // stable addresses
     gf::ScanArgs *d_args = nullptr;
     double *d_jmu = nullptr;
     Stage stage[kStages];
@@ -219,6 +225,8 @@ struct gf_server {
     bool admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
                    std::vector<Upload> &uploads);
     Table *ensure_table(const std::string &key, const Request &r, bool *fits);
+    hipError_t add_group_buffer();
+    bool place(Table &t, bool group);
     void evict_tables();
     void finish(Request *r);
     int fail_worker(hipError_t e, const char *what);
@@ -238,6 +246,10 @@ std::string key_angular(const gf_quadrature &q, const gf_params &p)
 {
     return "a" + std::to_string(q.n_angular) + ":" + std::to_string(q.angular_rule) + ":" +
            std::to_string(p.dimension == 0 ? 4 : p.dimension);
+}
+std::string key_groups(const gf_quadrature &q, const gf_params &p)
+{
+    return "g" + key_angular(q, p);
 }
 std::string key_arc(const gf_quadrature &q) { return "c" + std::to_string(q.n_arc); }
 
@@ -276,9 +288,7 @@ void gf_server::evict_tables()
 {
     for (auto jt = tables.begin(); jt != tables.end();) {
         if (jt->second.refs == 0) {
-            arena.release(jt->second.off, jt->second.bytes);
-            if (!jt->second.grp_host.empty())
-                groups_arena.release(jt->second.grp_off, jt->second.grp_host.size());
+            jt->second.from->release(jt->second.off, jt->second.bytes);
             jt = tables.erase(jt);
         } else {
             ++jt;
@@ -286,7 +296,37 @@ void gf_server::evict_tables()
     }
 }
 
-// Builds (or finds) a table in the arena; *fits = false if it cannot be
+hipError_t gf_server::add_group_buffer()
+{
+    // another thread may be capturing a graph: an allocation here must not break it
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    char *d = nullptr;
+    const hipError_t e = hipMalloc(&d, kGroupBufferBytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) return e;
+    groups.emplace_back();
+    groups.back().d = d;
+    groups.back().arena.init(kGroupBufferBytes);
+    return hipSuccess;
+}
+
+// Finds room for a table: in the budgeted arena, or (group) in the group buffers.
+bool gf_server::place(Table &t, bool group)
+{
+    auto take = [&](Arena &from, char *base) {
+        if (!from.alloc(t.bytes, &t.off)) return false;
+        t.from = &from;
+        t.dev = base + t.off;
+        return true;
+    };
+    if (!group) return take(arena, d_arena);
+    for (GroupBuffer &b : groups)
+        if (take(b.arena, b.d)) return true;
+    return false;
+}
+
+// Builds (or finds) a table in its arena; *fits = false if it cannot be
 // placed now.  Called with the lock held.
 Table *gf_server::ensure_table(const std::string &key, const Request &r, bool *fits)
 {
@@ -305,15 +345,20 @@ Table *gf_server::ensure_table(const std::string &key, const Request &r, bool *f
         std::vector<float> ang32;
         gf::angular_tables(r.q.n_angular, r.q.angular_rule, r.p.dimension == 0 ? 4 : r.p.dimension,
                            ang, ang32, &t.wmid);
-        std::vector<double> grp;
-        gf::group_table(r.q.n_angular, r.q.angular_rule, ang, t.wmid, grp);
         const size_t b64 = gf::align256(ang.size() * sizeof(double));
         t.host.assign(b64 + ang32.size() * sizeof(float), 0);
         std::memcpy(t.host.data(), ang.data(), ang.size() * sizeof(double));
         std::memcpy(t.host.data() + b64, ang32.data(), ang32.size() * sizeof(float));
         t.off32 = b64;
-        t.grp_host.resize(grp.size() * sizeof(double));
-        if (!grp.empty()) std::memcpy(t.grp_host.data(), grp.data(), t.grp_host.size());
+    } else if (key[0] == 'g') {
+        std::vector<double> ang, grp;
+        std::vector<float> ang32;
+        double wmid;
+        gf::angular_tables(r.q.n_angular, r.q.angular_rule, r.p.dimension == 0 ? 4 : r.p.dimension,
+                           ang, ang32, &wmid);
+        gf::group_table(r.q.n_angular, r.q.angular_rule, ang, wmid, grp);
+        t.host.resize(grp.size() * sizeof(double));
+        std::memcpy(t.host.data(), grp.data(), t.host.size());
     } else {
         std::vector<double> arc;
         gf::arc_table(r.q.n_arc, arc);
@@ -321,17 +366,17 @@ Table *gf_server::ensure_table(const std::string &key, const Request &r, bool *f
         std::memcpy(t.host.data(), arc.data(), t.host.size());
     }
     t.bytes = t.host.size();
-    auto place = [&] {
-        if (!arena.alloc(t.bytes, &t.off)) return false;
-        if (t.grp_host.empty() || groups_arena.alloc(t.grp_host.size(), &t.grp_off)) return true;
-        arena.release(t.off, t.bytes);
-        return false;
-    };
-    if (!place()) {
+    const bool group = key[0] == 'g';
+    if (!place(t, group)) {
         evict_tables();
-        if (!place()) {
-            *fits = false;
-            return nullptr;
+        if (!place(t, group)) {
+            // group coefficients are not part of the budget: they take another buffer
+            const bool more = group && add_group_buffer() == hipSuccess && place(t, true);
+            if (group && !more) (void)hipGetLastError();
+            if (!more) {
+                *fits = false;
+                return nullptr;
+            }
         }
     }
     auto res = tables.emplace(key, std::move(t));
@@ -352,13 +397,13 @@ bool gf_server::admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
     // Each table is pinned (refs raised) as soon as it is found or built, so
     // that building the next one cannot evict it; every failure below unpins
     // what this call pinned and returns the output range.
-    Table *tb[3] = {nullptr, nullptr, nullptr};
+    Table *tb[4] = {};
     auto undo = [&](int pinned) {
         for (int k = 0; k < pinned; ++k) --tb[k]->refs;
         arena.release(out_off, r->out_bytes);
         return false;
     };
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < r->n_keys; ++k) {
         bool fits;
         tb[k] = ensure_table(r->keys[k], *r, &fits);
         if (!fits) return undo(k);
@@ -367,21 +412,15 @@ bool gf_server::admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
     // staging space for new table contents: reserved for all of them before
     // any is marked uploaded, so a failed admission stages nothing
     size_t need = st.used;
-    for (int k = 0; k < 3; ++k)
-        if (!tb[k]->uploaded)
-            need = gf::align256(gf::align256(need) + tb[k]->bytes) + tb[k]->grp_host.size();
-    if (need > st.bytes) return undo(3);
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < r->n_keys; ++k)
+        if (!tb[k]->uploaded) need = gf::align256(need) + tb[k]->bytes;
+    if (need > st.bytes) return undo(r->n_keys);
+    for (int k = 0; k < r->n_keys; ++k) {
         if (tb[k]->uploaded) continue;
         size_t doff;
         void *h = st.bump(tb[k]->bytes, &doff);
         std::memcpy(h, tb[k]->host.data(), tb[k]->bytes);
-        uploads.push_back(Upload{doff, d_arena + tb[k]->off, tb[k]->bytes});
-        if (!tb[k]->grp_host.empty()) {
-            h = st.bump(tb[k]->grp_host.size(), &doff);
-            std::memcpy(h, tb[k]->grp_host.data(), tb[k]->grp_host.size());
-            uploads.push_back(Upload{doff, d_groups + tb[k]->grp_off, tb[k]->grp_host.size()});
-        }
+        uploads.push_back(Upload{doff, tb[k]->dev, tb[k]->bytes});
         tb[k]->uploaded = true;
     }
     r->out_off = out_off;
@@ -389,15 +428,16 @@ bool gf_server::admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
     free_slots.pop_back();
     gf::ScanArgs &a = r->args;
     gf::fill_constants(a, r->p, r->has_props ? &r->props : nullptr, r->q);
-    a.rad = reinterpret_cast<const double *>(d_arena + tb[0]->off);
-    a.ang = reinterpret_cast<const double *>(d_arena + tb[1]->off);
-    a.ang32 = reinterpret_cast<const float *>(d_arena + tb[1]->off + tb[1]->off32);
-    a.grp = reinterpret_cast<const double *>(d_groups + tb[1]->grp_off);
-    a.n_grp = r->q.precision == GF_PREC_FP64
-                  ? gf::group_count(r->q.n_angular, r->q.angular_rule) : 0;
-    a.grp_mid = gf::group_has_middle(r->q.angular_rule);
+    a.rad = reinterpret_cast<const double *>(tb[0]->dev);
+    a.ang = reinterpret_cast<const double *>(tb[1]->dev);
+    a.ang32 = reinterpret_cast<const float *>(tb[1]->dev + tb[1]->off32);
+    if (tb[3]) {
+        a.grp = reinterpret_cast<const double *>(tb[3]->dev);
+        a.n_grp = gf::group_count(r->q.n_angular, r->q.angular_rule);
+        a.grp_mid = gf::group_has_middle(r->q.angular_rule);
+    }
     a.wmid = tb[1]->wmid;
-    a.arc = reinterpret_cast<const double *>(d_arena + tb[2]->off);
+    a.arc = reinterpret_cast<const double *>(tb[2]->dev);
     a.jmu = d_jmu + 2 * (GF_MAX_TAYLOR + 1) * (size_t)r->slot;
     // cannot fail: one lane per point on a grid checked at submission (at
     // most 2^31 points, 2^25 tiles)
@@ -687,7 +727,7 @@ int gf_server_create(const gf_server_config *cfg, gf_server_t **out)
     for (int k = 0; e == hipSuccess && k < kComputeStreams; ++k)
         e = hipStreamCreateWithFlags(&s->comp[k], hipStreamNonBlocking);
     if (e == hipSuccess) e = hipMalloc(&s->d_arena, cfg->device_budget_bytes);
-    if (e == hipSuccess) e = hipMalloc(&s->d_groups, kGroupArenaBytes);
+    if (e == hipSuccess) e = s->add_group_buffer();
     if (e == hipSuccess) e = hipMalloc(&s->d_args, sizeof(gf::ScanArgs) * cfg->max_inflight);
     if (e == hipSuccess)
         e = hipMalloc(&s->d_jmu, 2 * sizeof(double) * (GF_MAX_TAYLOR + 1) * cfg->max_inflight);
@@ -709,7 +749,6 @@ int gf_server_create(const gf_server_config *cfg, gf_server_t **out)
     s->fill_min = std::min<long long>(3 * waves / 2, kMaxItemsPerBatch);
     s->fill_max = std::min<long long>(6 * waves, kMaxItemsPerBatch);
     s->arena.init(cfg->device_budget_bytes);
-    s->groups_arena.init(kGroupArenaBytes);
     for (int k = cfg->max_inflight - 1; k >= 0; --k) s->free_slots.push_back(k);
     s->worker = std::thread([s] { s->run(); });
     *out = s;
@@ -759,6 +798,9 @@ int gf_server_submit_ex(gf_server_t *s, const gf_params *params, const gf_propag
     r->keys[0] = key_radial(*quad, *params);
     r->keys[1] = key_angular(*quad, *params);
     r->keys[2] = key_arc(*quad);
+    if (quad->precision == GF_PREC_FP64 && !(props && props->numerator) &&
+        gf::group_count(quad->n_angular, quad->angular_rule) > 0)
+        r->keys[r->n_keys++] = key_groups(*quad, *params);
     // one lane per point: the batch already fills the GPU with many requests,
     // and whole 64-point tiles waste no lanes on short node lists
     r->lanes = 1;
@@ -874,7 +916,7 @@ int gf_server_release(gf_server_t *s, uint64_t ticket)
     if (r->state != GF_REQ_DONE) return fail(GF_EINVAL, "request %llu is not done", (unsigned long long)ticket);
     if (r->slot >= 0) {
         s->arena.release(r->out_off, r->out_bytes);
-        for (int k = 0; k < 3; ++k) {
+        for (int k = 0; k < r->n_keys; ++k) {
             auto jt = s->tables.find(r->keys[k]);
             if (jt != s->tables.end()) --jt->second.refs;
         }
@@ -953,7 +995,7 @@ int gf_server_destroy(gf_server_t *s)
     if (s->d_jmu) (void)hipFree(s->d_jmu);
     if (s->d_args) (void)hipFree(s->d_args);
     if (s->d_arena) (void)hipFree(s->d_arena);
-    if (s->d_groups) (void)hipFree(s->d_groups);
+    for (GroupBuffer &b : s->groups) (void)hipFree(b.d);
     if (s->stream) (void)hipStreamDestroy(s->stream);
     for (int k = 0; k < kComputeStreams; ++k)
         if (s->comp[k]) (void)hipStreamDestroy(s->comp[k]);
