@@ -270,7 +270,7 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a)
     constexpr bool tail = L == 1 || (PREC == kFp32c && L == 2);
     const float *lds = nullptr;
     if constexpr (LDS) {
-        __shared__ float squares[kLdsPairs];
+        __shared__ __align__(16) float squares[kLdsPairs];  // read as float4
         load_squares(a, squares, threadIdx.x & 63);
         lds = squares;
     }
@@ -292,7 +292,7 @@ __device__ __forceinline__ void serve_loop(const ScanArgs *reqs, const WorkItem 
     const float *lds = nullptr;
     float *squares = nullptr;
     if constexpr (LDS) {
-        __shared__ float waves[4][kLdsPairs];  // a slice for each wave of the block
+        __shared__ __align__(16) float waves[4][kLdsPairs];  // a slice for each wave of the block
         lds = squares = waves[threadIdx.x >> 6];
     }
     for (;;) {
