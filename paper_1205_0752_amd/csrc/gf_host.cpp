@@ -222,11 +222,11 @@ void angular_tables(int na, int rule, int dim, std::vector<double> &ang,
 // last group) and 28 per contour node for the powers; pair by pair it is 59
 // slots per eight pairs, 31 per four, 11 per single pair and 12 for a middle
 // node.  The groups are taken where they save a tenth, which pays for their
-// larger code: from 34 pairs on always (16 pairs, 64^2 points at 64 lanes each:
-// 11.9 us in groups, 11.0 by pairs; 64 pairs: 19.2 and 20.6).
-int group_count(int na, int rule)
+// larger code (16 pairs, 64^2 points at 64 lanes each: 11.9 us in groups, 11.0 by pairs;
+// 64 pairs: 19.2 and 20.6): at every n_a >= 83, and below that where the nodes nearly
+// fill their groups (31, 45-48, 55, 57-64, 69-71, 73-80).
+int group_count(int na)
 {
-    (void)rule;
     const int np = na / 2, nodes = np + na % 2;
     const int groups = (nodes + kGroupNodes - 1) / kGroupNodes;
     const int grouped = 42 * groups + 4 * (groups % 2) + 28;
@@ -237,7 +237,7 @@ int group_count(int na, int rule)
 size_t group_doubles(int na, int rule)
 {
     // one group more than the tables hold: the sums load a group ahead
-    const size_t n = group_count(na, rule);
+    const size_t n = group_count(na);
     return n ? kGroupDoubles * (n * (group_has_middle(rule) ? 2 : 1) + 1) : 0;
 }
 
@@ -256,7 +256,7 @@ size_t group_doubles(int na, int rule)
 void group_table(int na, int rule, const std::vector<double> &ang, double wmid,
                  std::vector<double> &grp)
 {
-    const int n_grp = group_count(na, rule), np = na / 2, nodes = np + na % 2;
+    const int n_grp = group_count(na), np = na / 2, nodes = np + na % 2;
     grp.assign(group_doubles(na, rule), 0.0);
     const int tables = group_has_middle(rule) ? 2 : 1;
     for (int b = 0; b < tables * n_grp; ++b) {
@@ -748,7 +748,7 @@ int gf_plan_ex(const gf_params *params, const gf_propagators *props, const gf_qu
     a.arc = reinterpret_cast<const double *>(base + off_arc);
     a.ang32 = reinterpret_cast<const float *>(base + off_a32);
     a.grp = reinterpret_cast<const double *>(base + off_grp);
-    a.n_grp = grouped ? gf::group_count(quad->n_angular, quad->angular_rule) : 0;
+    a.n_grp = grouped ? gf::group_count(quad->n_angular) : 0;
     a.grp_mid = gf::group_has_middle(quad->angular_rule);
     a.wmid = wmid;
 

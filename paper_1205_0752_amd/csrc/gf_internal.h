@@ -162,10 +162,10 @@ void gauss_legendre(int n, std::vector<double> &x, std::vector<double> &w);
 void radial_table(int n_r, double lambda2, int dim, int split, std::vector<double> &rad);
 void angular_tables(int n_a, int rule, int dim, std::vector<double> &ang,
                     std::vector<float> &ang32, double *wmid);
-// Groups the angular sums of this rule run in (0: pair by pair), whether they
-// have a second table, the doubles of both, and their coefficients from the
+// Groups the angular sums of a rule of n_a nodes run in (0: pair by pair), whether the
+// rule has a second table, the doubles of both, and their coefficients from the
 // pair table and middle weight.
-int group_count(int n_a, int rule);
+int group_count(int n_a);
 inline bool group_has_middle(int rule) { return rule != GF_ANG_TANH_SINH; }
 size_t group_doubles(int n_a, int rule);
 void group_table(int n_a, int rule, const std::vector<double> &ang, double wmid,

@@ -277,7 +277,7 @@ extern "C" int gf_scan_noalloc(const gf_params *params, const gf_grid *grid,
     a.jmu = reinterpret_cast<const double *>(base + off_jmu);
     a.wmid = middle_weight(quad->n_angular, quad->angular_rule, dim);
     a.grp = reinterpret_cast<const double *>(base + off_grp);
-    a.n_grp = grouped ? group_count(quad->n_angular, quad->angular_rule) : 0;
+    a.n_grp = grouped ? group_count(quad->n_angular) : 0;
     a.grp_mid = group_has_middle(quad->angular_rule);
     const int lanes = auto_lanes(a, quad->precision, *grid);
     if ((rc = set_grid(a, *grid, lanes)) != GF_OK) return rc;

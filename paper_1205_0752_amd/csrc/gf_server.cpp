@@ -433,7 +433,7 @@ bool gf_server::admit_one(Request *r, Stage &st, std::vector<Request *> &fresh,
     a.ang32 = reinterpret_cast<const float *>(tb[1]->dev + tb[1]->off32);
     if (tb[3]) {
         a.grp = reinterpret_cast<const double *>(tb[3]->dev);
-        a.n_grp = gf::group_count(r->q.n_angular, r->q.angular_rule);
+        a.n_grp = gf::group_count(r->q.n_angular);
         a.grp_mid = gf::group_has_middle(r->q.angular_rule);
     }
     a.wmid = tb[1]->wmid;
@@ -799,7 +799,7 @@ int gf_server_submit_ex(gf_server_t *s, const gf_params *params, const gf_propag
     r->keys[1] = key_angular(*quad, *params);
     r->keys[2] = key_arc(*quad);
     if (quad->precision == GF_PREC_FP64 && !(props && props->numerator) &&
-        gf::group_count(quad->n_angular, quad->angular_rule) > 0)
+        gf::group_count(quad->n_angular) > 0)
         r->keys[r->n_keys++] = key_groups(*quad, *params);
     // one lane per point: the batch already fills the GPU with many requests,
     // and whole 64-point tiles waste no lanes on short node lists

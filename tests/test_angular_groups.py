@@ -207,3 +207,29 @@ def test_y_plane_at_the_pole_without_a_cut(n_a):
         assert np.all(np.abs(g - want) <= 64 * EPS * np.abs(want))
         assert np.all(np.isfinite(gf.yscan_plan(plan, 1e-30 + 1e-30j, grid, 0).cpu().numpy()))
     plan.close()
+
+
+@pytest.mark.parametrize("n_a", [30, 31, 32, 44, 45, 49, 55, 56, 57, 65, 68, 69, 72, 73, 81, 82, 83])
+def test_orders_on_both_sides_of_the_form_switches(n_a):
+    q = Quadrature(32, n_a, 9)
+    g, c = _scan(HEAVY, q, 2)
+    go, co, cond = oracle.scan(HEAVY, q, GRID, want_cond=True)
+    assert np.array_equal(c, co)
+    ok = co != oracle.SINGULAR
+    check_fp64(g[ok], go[ok], cond[ok])
+
+
+@pytest.mark.parametrize("n_a,rule", [(512, GC2), (113, GC2), (129, TANH_SINH)])
+def test_far_along_the_cut(n_a, rule):
+    """|x| = 1000 m^2 next to the negative axis: e ~ m^2 / |x| about y = x, where the first
+    table is taken with Re e < 0."""
+    p, q = Params(1.0, 1.0, 1.0, 1e6), Quadrature(96, n_a, 16, gf.FP64, rule)
+    grid = Grid(12, 14, -1200.0, -900.0, -35.0, 35.0)
+    x = oracle.grid_points(grid)
+    _, co, cond = oracle.eval_points(p, q, x, want_cond=True)
+    go = oracle.eval_points_q_sets(p, q, x)
+    plan = gf.Plan(p, q)
+    for lanes in (1, 16):
+        g = gf.scan_plan(plan, grid, lanes=lanes).cpu().numpy().ravel()
+        check_fp64(g, go, cond)
+    plan.close()
