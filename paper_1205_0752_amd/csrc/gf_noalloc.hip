@@ -76,10 +76,12 @@ __device__ void legendre_quotients(int n, double *b)
 // Written P_{m+1} = (1 + b_m) t P_m - b_m P_{m-1} with the quotients b from a table,
 // the chain is one FMA a step (a division and two multiplies before).  The
 // Legendre equation gives the second and third derivatives with the first, so the
-// node and P' there are right to third order in dr, and with
+// node and P' there are right to second order in dr, and with
 // (n dr)^2 < 1e-13 (1 - r^2) the rest is below rounding: two values of P_n do
-// (four or five before), weights as exact as before (n = 96: 4e-14 at worst, 1.7e-13
-// before).  256 + 96 + 16 nodes: 77 us -> 10 us.
+// (four or five before).  1 - r^2 is taken as (1 - r)(1 + r), at the node before its rounding
+// (rho), where P' stands: weights within 6e-15 at n = 64, 3e-14 at 96, 4e-13 at 512, 2e-11 at
+// 8192 (the host's rule 9e-14, 1.7e-13, 2e-13, 1.6e-9; without rho and the product 4e-14,
+// 4e-14, 2e-12, 9e-10).  256 + 96 + 16 nodes: 77 us -> 10 us.
 __device__ void gl_node(int n, int k, const double *b, double *x, double *w)
 {
     const int i = 2 * k < n ? k + 1 : n - k;
@@ -96,20 +98,22 @@ __device__ void gl_node(int n, int k, const double *b, double *x, double *w)
             pk = next;
         }
     };
-    double dp = 1.0;
+    double dp = 1.0, rho = 0.0;
     for (int it = 0; it < 64; ++it) {
         legendre(r);
-        const double q = 1.0 - r * r, nn = n * (n + 1.0);
+        const double q = (1.0 - r) * (1.0 + r), nn = n * (n + 1.0);
         dp = n * (pkm1 - r * pk) / q;
         const double dr = pk / dp;
         const double d2 = (2.0 * r * dp - nn * pk) / q;
         const double d3 = (4.0 * r * d2 - (nn - 2.0) * dp) / q;
         const bool last = n * dr * (n * dr) < 1e-13 * q;
-        r -= dr + 0.5 * dr * dr * (d2 / dp);
-        dp += dr * (0.5 * dr * d3 - d2);
+        const double c = d2 / dp, step = dr + 0.5 * dr * dr * c, next = r - step;
+        rho = (r - next) - step;
+        r = next;
+        dp += dr * (0.5 * dr * (d3 - d2 * c) - d2);
         if (last) break;
     }
-    *w = 2.0 / ((1.0 - r * r) * dp * dp);
+    *w = 2.0 / (((1.0 - r) * (1.0 + r) - 2.0 * r * rho) * dp * dp);
     *x = (n % 2 == 1 && 2 * k + 1 == n) ? 0.0 : (2 * k < n ? -r : r);
 }
 
