@@ -49,6 +49,8 @@ FLOPS_PER_EVAL_UNFOLDED = 13.0
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "scan_kernel_fp64_bench_workload_traffic.json")
 FLOPS_FILE = os.path.join(ROOT, "profiles", "scan_kernel_fp64_bench_workload_flops.json")
+# HBM traffic and FP64 flops per launch of the scan kernels, by kernel name
+COUNTERS_FILE = os.path.join(ROOT, "profiles", "scan_kernels_launch_counters.json")
 # the sources that define the scan kernels' machine code
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1205_0752_amd", "csrc", name)
                   for name in ("gf_internal.h", "gf_device.h", "gf_scan.h", "gf_scan_groups.hip",
@@ -93,6 +95,20 @@ def measured_flops(kernel: str):
     if rec.get("kernel") != kernel or rec.get("kernels_source_sha256") != sha:
         return None
     return float(rec["fp64_flops_per_launch"])
+
+
+def launch_counters(kernel: str):
+    """The committed counters of one launch of `kernel` on the bench workload
+    (traffic_bytes, fp64_flops), or None when there are none for this kernel or its
+    sources have changed since they were taken."""
+    try:
+        with open(COUNTERS_FILE) as f:
+            rec = json.load(f)
+        if rec.get("kernels_source_sha256") != kernel_source_sha256():
+            return None
+    except (OSError, ValueError):
+        return None
+    return rec["kernels"].get(kernel)
 
 
 def roofline_conventions(evals: int, sec: float, peak: float, kernel: str):
@@ -220,15 +236,28 @@ def cpu_worker(n_points: int) -> int:
     return 0
 
 
+def angular_groups(n_angular: int) -> int:
+    """Groups of eight folded nodes that an FP64 rule's sums run in (0: pair by
+    pair), by the library's rule (group_count)."""
+    pairs, odd = divmod(n_angular, 2)
+    groups = (pairs + odd + 7) // 8
+    grouped = 42 * groups + 4 * (groups % 2) + 28
+    single = 59 * (pairs // 8) + 31 * (pairs % 8 // 4) + 11 * (pairs % 4) + 12 * odd
+    return groups if 10 * grouped < 9 * single else 0
+
+
 def scan_kernel_name(params, quad, lanes, props=None):
-    """The kernel instance a scan launches: scan_kernel_<prec><L, TAYLOR, SPLIT,
-    POLES> (pole sums always run the instance with the t^n epilogue)."""
+    """The kernel instance a scan launches: scan_kernel_<form><L, TAYLOR, SPLIT,
+    POLES> (pole sums always run the instance with the t^n epilogue).  FP64 sums run in
+    groups, or over the pairs for short rules and numerators; FP32C scans of long rules
+    on many waves run scan_kernel_fp32c_w6<L, TAYLOR>, which this leaves out."""
     poles = props is not None
     taylor = poles or getattr(params, "taylor_order", 0) > 0
     split = bool(getattr(quad, "radial_split", 0)) and not poles
     b = lambda v: "true" if v else "false"  # noqa: E731
-    return (f"scan_kernel_{'fp64' if quad.precision == 0 else 'fp32c'}<{lanes}, {b(taylor)}, "
-            f"{b(split)}, {b(poles)}>")
+    grouped = angular_groups(quad.n_angular) > 0 and not getattr(props, "numerator", ())
+    form = "fp32c" if quad.precision != 0 else "fp64" if grouped else "fp64_pairs"
+    return f"scan_kernel_{form}<{lanes}, {b(taylor)}, {b(split)}, {b(poles)}>"
 
 
 def time_scan(gf, torch, params, grid, quad, steps, warmup, lanes, props=None, latency_scans=0):
@@ -521,6 +550,7 @@ def main() -> int:
                   latency_scans=args.latency_scans)
     peak = FP64_PEAK_TFLOPS if quad.precision == 0 else FP32_PEAK_TFLOPS
     progress(f"timed scans: {t['ms']:.3f} ms per step")
+    counters = (launch_counters(t["kernel"]) or {}) if args.config == "c1_fp64_1024sq" else {}
     result = {
         "metric": "complex grid points/s & integrand evals/s (FP64 vs FP32+compensated); "
                   "p99 scan latency",
@@ -552,8 +582,9 @@ def main() -> int:
                      "unit": "TFLOP/s",
                      "frac": t["tflops"] / (FP64_PEAK_TFLOPS if quad.precision == 0
                                             else FP32_PEAK_TFLOPS),
-                     "traffic": (measured_traffic(t["kernel"])
-                                 if args.config == "c1_fp64_1024sq" else None),
+                     "traffic": counters.get("traffic_bytes", measured_traffic(t["kernel"])
+                                             if args.config == "c1_fp64_1024sq" else None),
+                     "hardware_fp64_flops": counters.get("fp64_flops"),
                      "kernel": t["kernel"], "flops_per_eval": FLOPS_PER_EVAL,
                      "conventions": (roofline_conventions(t["evals"], t["sec"], peak, t["kernel"])
                                      if quad.precision == 0 else None)},
