@@ -835,12 +835,15 @@ __device__ __forceinline__ cd angular_sum64(const double *table, int npair, doub
 // Accuracy: an expansion about one centre loses sum |coefficient| |v|^k / |P|.
 // There are two tables.  v = e, about the cut's end s = 1: P = prod (e + 1 - s_j) has
 // only positive coefficients, so nothing is lost for Re e >= 0 however close to
-// the end, and little where |Im e| >= min(2, 4.5 |e|) |Re e| or |e| >= 3 (at most 45
-// eps of the sum, 3 in the median).  That covers nearly all nodes of a ray, where
+// the end (at most 7 eps of the sum, 1 in the median), and little where |Im e| >=
+// min(2, 4.5 |e|) |Re e| or |e| >= 3: at most 26 eps down to |e| = 0.05, and below that
+// 0.5 / |e| where a node sits at 1 - s = |e| (up to 375 eps, on tanh-sinh; 1 in the
+// median), where the direct denominators, whose U^2 has lost that much of e, are off
+// by up to 125 / |e|.  That covers nearly all nodes of a ray, where
 // e = (|x| - r)^2 / (4 |x| r) plus a term of order m1^2 / |x|.  v = e + 1/2, about
 // the middle, for the rest: a group's nodes being spread over (0, 1), the loss
 // stays below about 10 where |sigma|^2 + |e|^2 <= 6 |sigma| |e|, down to the ratio
-// kCutSensitivity from the cut (at most 46 eps, 1.7 in the median).  The pair
+// kCutSensitivity from the cut (at most 31 eps, 1.3 in the median).  The pair
 // sums' quadratic loses up to 45 to 90 eps at its limit, 4 in the median
 // there.  Nodes that neither takes (0.5 to 3 % of a scan, 6 % of one along the
 // cut) and |e| >= 2^30 (two groups' |P|^2 multiply up to |v|^32) or V^2 = 0 run

@@ -248,11 +248,11 @@ size_t group_doubles(int na, int rule)
 // the sum of the weights.  Missing nodes are filled up with weight 0 at a place
 // where the table is never used, since their factor of N and P vanishes there:
 // s = 0 in the first table, whose centre is s = 1 (e = -1; at e = 0, the cut's end,
-// the sum is finite), and the centre in the second, whose centre is 1/2 (on the cut).  Tanh-sinh has no
-// second one: half of its nodes lie within 1e-2 of s = 1, where an expansion
-// about the middle would cancel (up to 1e5 eps next to that end; about s = 1 at
-// most 16).  The products run in long double, so the coefficients are rounded
-// once.
+// the sum is finite), and the centre in the second, whose centre is 1/2 (on the cut).
+// Tanh-sinh has no second one: half of its nodes lie within 1e-2 of s = 1, where an
+// expansion about the middle would cancel (up to 1e5 eps next to that end; about s = 1
+// as the other rules).  The products run in long double, so the coefficients are
+// rounded once.
 void group_table(int na, int rule, const std::vector<double> &ang, double wmid,
                  std::vector<double> &grp)
 {

@@ -26,7 +26,8 @@ namespace {
 
 // One wave's tile of grid points: STEP 4 (the point) and STEP 5 (eq. 15 on
 // the point's contour), shared by the one-grid scan and the serving kernel so a
-// point's result does not depend on which launch computes it.
+// point's result at L lanes does not depend on which launch computes it (other L sum
+// in another order, and L > 4 leaves the groups' second table out).
 // TAYLOR = false compiles out the t^n (n >= 1) epilogue, so the order-0 scan
 // carries no extra live values; both forms compute order 0 identically.
 // Tiles are numbered row-major over the rows from row0 on, tiles_a per row.

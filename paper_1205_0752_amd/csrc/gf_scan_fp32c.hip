@@ -4,14 +4,15 @@
 namespace gf {
 namespace {
 
-// Waves per SIMD the registers are budgeted for: five where the inner loop is most
-// of a plain scan (six hide its latency a little better, but spill more around
-// it: 1024^2 at 512 x 256 nodes, two lanes, 10.54 ms at six, 10.70 at five, 11.12
-// at four; 512^2 at 64 x 32 0.208, 0.172, 0.148; 600 x 400 at 400 x 400, eight lanes,
-// 3.27, 3.24, 3.43).  The forms with more per node take four (512^2 at 256 x 128:
-// pole sums 2.67 ms at six, 2.09 at four, with a numerator 5.10, 2.96; 1024^2 split
-// rule 5.45, 4.37), and so do many lanes per point, where a wave is mostly set-up
-// (200 x 150 at 64 x 64: 50.6, 43.3 us).
+// Waves per SIMD the registers are budgeted for: at up to eight lanes of a plain scan
+// five, a compromise.  Long node loops want six, which hide the inner loop's latency
+// better, short ones four, which spill less around it (ms at six, five, four: 1024^2 at
+// 512 x 256 nodes, two lanes, 10.54, 10.70, 11.12; 600 x 400 at 400 x 400, eight lanes, 3.27,
+// 3.24, 3.43; 512^2 at 64 x 32 0.208, 0.172, 0.148); six everywhere was slower than five
+// on short rules by more than it gained on long ones.  The forms with more per node
+// take four (512^2 at 256 x 128: pole sums 2.67 ms at six, 2.09 at four, with a numerator
+// 5.10, 2.96; 1024^2 split rule 5.45, 4.37), and so do many lanes per point, where a wave
+// is mostly set-up (200 x 150 at 64 x 64: 50.6, 43.3 us).
 template <int L, bool SPLIT, bool POLES>
 constexpr int kWaves = POLES || SPLIT || L >= 16 ? 4 : 5;
 
